@@ -113,10 +113,11 @@ typedef struct spkadd_opts {
   float load_factor_sym; /* max (input entries / table slots) of symbolic tables; 0 = auto */
   float load_factor_num; /* max (output entries / table slots) of numeric tables, <= 0.5; 0 = auto */
   float window_fill;     /* target fill of a row window relative to window_cap; 0 = auto */
-  int32_t accum_mode;    /* wave bins: 0 = auto (bitmap where dense enough, else hash),
-                            1 = hash tables only, 2 = bitmap wherever it fits (m <= 131072) */
-  float bitmap_ratio;    /* auto mode: use the bitmap when ceil(m / 8192) <= bitmap_ratio * E,
-                            E = ceil(u_max / 64) of the bin; 0 = default (1.0) */
+  int32_t accum_mode;    /* wave bins: 0 = auto (bitmap over all rows where dense enough, else a
+                            bitmap over the column's non-empty 64-row blocks), 1 = hash tables
+                            only, 2 = bitmap over all rows wherever it fits (m <= 131072) */
+  float bitmap_ratio;    /* auto mode: use the bitmap over all rows when ceil(m / 8192) <=
+                            bitmap_ratio * E, E = ceil(u_max / 64) of the bin; 0 = default (1.0) */
   int32_t wave_merge;    /* 0 = merge two adjacent wave bins that each hold >= 1/16 of the
                             wave columns (one kernel then reads neighbouring columns together);
                             1 = keep every wave bin separate */
@@ -159,8 +160,8 @@ void spkadd_opts_default(spkadd_opts* opts);
  *            which reads the bins on the device.  The row windows are then built in
  *            that call.  The plan waits here instead (once for the bin counts, a
  *            few more times for row windows) when SPKADD_FLAG_VALIDATE is set, when
- *            some rowidx pointer is NULL, and when k > 64 or load_factor_num is not
- *            0.5 (the wave bins then take one launch each).
+ *            some rowidx pointer is NULL, and when k > 128 (k > 64 with hash tables) or
+ *            load_factor_num is not 0.5 (the wave bins then take one launch each).
  * Errors: INVALID (null pointers, k < 1, negative sizes, bad option values, or
  * malformed inputs when SPKADD_FLAG_VALIDATE is set), OOM, HIP; OVERFLOW (some u_j
  * above INT32_MAX) here when the plan waits, else from spkadd_symbolic.

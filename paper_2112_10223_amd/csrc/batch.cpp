@@ -128,14 +128,26 @@ KArgs slot_args(const spkadd_batch_s* b, const ShapeKey& key, int wi, bool bm, b
   int nq_bin = key.nq_max;
   if (bm && b->args.accum_mode == SPKADD_ACCUM_AUTO)
     while (nq_bin > 1 && !((float)nq_bin <= b->args.bitmap_ratio * (float)wave_bin_E(bin))) --nq_bin;
-  lds_layout_pipe(bin, numeric, vb, ts, bm ? nq_bin : 0, a);
-  if (bm) {
+  if (!bm) {
+    if (b->args.accum_mode == SPKADD_ACCUM_HASH) {
+      lds_layout_pipe(bin, numeric, vb, ts, ACC_HASH, 0, 64, a);
+      return a;
+    }
+    // the ranked bitmap: room for every request's levels, whatever its m
+    lds_layout_pipe(bin, numeric, vb, ts, ACC_RANKED, RANKED_WORST_M, 64, a);
+    KArgs t{};
+    lds_layout_pipe(bin, numeric, vb, ts, ACC_RANKED, RANKED_WORST_M + 1, 64, t);
+    if (t.slice_bytes > a.slice_bytes) a.slice_bytes = t.slice_bytes;
+    return a;
+  }
+  lds_layout_pipe(bin, numeric, vb, ts, ACC_BITMAP, nq_bin, 64, a);
+  {
     // each request lays out its own slice for its bitmap size; a smaller bitmap
     // can need more room (its staged rows and values may not fit over it), so
     // the launch slice is the largest over every size up to the bin's maximum
     for (int nq = 1; nq < nq_bin; ++nq) {
       KArgs t{};
-      lds_layout_pipe(bin, numeric, vb, ts, nq, t);
+      lds_layout_pipe(bin, numeric, vb, ts, ACC_BITMAP, nq, 64, t);
       if (t.slice_bytes > a.slice_bytes) a.slice_bytes = t.slice_bytes;
     }
   }

@@ -11,7 +11,7 @@ namespace spk {
 // each run of one request goes through run_pipe with that request's arguments, its
 // LDS layout computed here when DEV_LAYOUT (always for bitmaps: it depends on the
 // request's m).  Numeric: requests whose outcome is not OK are skipped.
-template <int E, bool NUM, typename V, bool BM, bool DEV_LAYOUT>
+template <int E, bool NUM, typename V, int ACC, bool DEV_LAYOUT>
 __device__ __forceinline__ void slot_chunks(const BatchArgs& b, const KArgs& a, int slot, unsigned char* base, int c0,
                                             int G) {
   const int lane = lane_id();
@@ -42,11 +42,12 @@ __device__ __forceinline__ void slot_chunks(const BatchArgs& b, const KArgs& a, 
         ta.colptr_c = q.colptr_c;
         ta.out_r = q.out_r;
         ta.out_v = q.out_v;
-        if (BM || DEV_LAYOUT) pipe_layout(E, NUM, (int)sizeof(V), ts, BM ? q.nq : 0, ta);
+        if (ACC != ACC_HASH || DEV_LAYOUT)
+          pipe_layout(E, NUM, (int)sizeof(V), ts, ACC, ACC == ACC_RANKED ? q.m : q.nq, 1, ta);
         // this run's columns, local to the request, in lanes 0 .. end - pos - 1
         const int src = min(lane + pos, nu - 1);
         const int ucol = __shfl(g, src) - q.col_base;
-        run_pipe<E, NUM, V, BM>(ta, base, end - pos, ucol);
+        run_pipe<E, NUM, V, ACC, 1>(ta, base, end - pos, ucol);
       }
       pos = end;
     }

@@ -7,13 +7,20 @@
 
 namespace spk {
 
+template <int E, bool NUM, typename V>
+__device__ __forceinline__ void slot_any(int bm, const BatchArgs& b, const KArgs& a, int slot, unsigned char* base,
+                                         int c0, int G) {
+  if (bm) slot_chunks<E, NUM, V, ACC_BITMAP, true>(b, a, slot, base, c0, G);
+  else if (b.accum_mode != 1) slot_chunks<E, NUM, V, ACC_RANKED, true>(b, a, slot, base, c0, G);
+  else slot_chunks<E, NUM, V, ACC_HASH, true>(b, a, slot, base, c0, G);
+}
+
 template <bool NUM, typename V>
 __device__ __forceinline__ void fused_slot(int wi, int bm, const BatchArgs& b, const KArgs& a, int slot,
                                            unsigned char* base, int c0, int G) {
 #define SPK_FUSED_CASE(I, E)                                                    \
   case I:                                                                       \
-    if (bm) slot_chunks<E, NUM, V, true, true>(b, a, slot, base, c0, G);        \
-    else slot_chunks<E, NUM, V, false, true>(b, a, slot, base, c0, G);          \
+    slot_any<E, NUM, V>(bm, b, a, slot, base, c0, G);                           \
     break;
   switch (wi) {
     SPK_FUSED_CASE(0, 1)
@@ -26,8 +33,7 @@ __device__ __forceinline__ void fused_slot(int wi, int bm, const BatchArgs& b, c
     SPK_FUSED_CASE(7, 10)
     SPK_FUSED_CASE(8, 12)
     default:
-      if (bm) slot_chunks<16, NUM, V, true, true>(b, a, slot, base, c0, G);
-      else slot_chunks<16, NUM, V, false, true>(b, a, slot, base, c0, G);
+      slot_any<16, NUM, V>(bm, b, a, slot, base, c0, G);
       break;
   }
 #undef SPK_FUSED_CASE
@@ -36,8 +42,12 @@ __device__ __forceinline__ void fused_slot(int wi, int bm, const BatchArgs& b, c
 // Persistent, one launch per pass for every wave slot.  The chunks of
 // all slots form one sequence, longest columns first; wavefront gw of G takes chunks
 // gw, gw + G, ... of that sequence.  The LDS slice is the largest any slot needs.
+// (Second launch bound: wavefronts per SIMD that the registers are held to.  Symbolic:
+// 136 registers otherwise, three wavefronts.  Numeric fp32 held to three spills: 155 ->
+// 182 us on sixteen requests of 9 million entries.)
 template <bool NUM, typename V>
-__global__ __launch_bounds__(64 * PIPE_WAVES_PER_BLOCK) void k_batch_fused(BatchArgs b, KArgs a) {
+__global__ __launch_bounds__(64 * PIPE_WAVES_PER_BLOCK, NUM ? 2 : 4) void k_batch_fused(
+    BatchArgs b, KArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int w = threadIdx.x >> 6;
   const int G = (int)gridDim.x * PIPE_WAVES_PER_BLOCK;

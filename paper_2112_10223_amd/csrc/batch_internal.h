@@ -29,7 +29,7 @@ struct BatchHdr {
 // Column slots: empty, too large for a wavefront, then (wave bin, accumulator).
 constexpr int BSLOT_EMPTY = 0;
 constexpr int BSLOT_LARGE = 1;
-constexpr int BSLOT_WAVE = 2;  // + 2 * (wave bin index) + (1 for the bitmap)
+constexpr int BSLOT_WAVE = 2;  // + 2 * (wave bin index) + (1 for the bitmap; else the ranked bitmap or hash tables)
 // Workgroup-sized columns (wave_max < u_j <= wg_max <= BATCH_WG_U, by default 1024
 // and 4096) of requests with at most BATCH_WG_SPAN rows: one workgroup bitmap each
 // (larger columns are left to the one-request path).
@@ -82,7 +82,4 @@ void launch_batch_wg(bool numeric, bool f64, int threads, const BatchArgs& b, co
 // Blocks of the fused kernel resident per CU with `lds` bytes of LDS per block (0 if
 // the query fails).
 int batch_fused_blocks_per_cu(bool numeric, bool f64, size_t lds);
-// LDS layout of a wave slice (same as the plain launch).
-void lds_layout_pipe(int bin, bool numeric, int vbytes, int ts_max, int bm_nq, KArgs& a);
-
 }  // namespace spk

@@ -227,13 +227,13 @@ __global__ __launch_bounds__(256) void k_batch_scatter(BatchArgs b) {
 
 // Persistent, one launch per (wave bin, accumulator): wavefront gw of G takes chunks
 // gw, gw + G, ... of its slot.
-template <int E, bool NUM, typename V, bool BM>
+template <int E, bool NUM, typename V, int ACC>
 __global__ __launch_bounds__(64 * PIPE_WAVES_PER_BLOCK) void k_batch_wave(BatchArgs b, KArgs a, int slot) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int w = threadIdx.x >> 6;
   const int G = (int)gridDim.x * PIPE_WAVES_PER_BLOCK;
   const int gw = xcd_remap(blockIdx.x, gridDim.x) * PIPE_WAVES_PER_BLOCK + w;
-  slot_chunks<E, NUM, V, BM, false>(b, a, slot, smem + w * a.slice_bytes, gw, G);
+  slot_chunks<E, NUM, V, ACC, false>(b, a, slot, smem + w * a.slice_bytes, gw, G);
 }
 
 // One workgroup per request: colptr(B_r) by an exclusive scan of its column counts.
@@ -268,36 +268,37 @@ void launch_batch_scan(const BatchArgs& b, hipStream_t s) {
   k_batch_scan<<<b.max_reqs, BATCH_SCAN_THREADS, 0, s>>>(b);
 }
 
-template <bool NUM, typename V, bool BM>
+template <bool NUM, typename V, int ACC>
 static void launch_bw(int wi, const BatchArgs& b, const KArgs& a, unsigned blocks, size_t lds, hipStream_t s) {
-  const int slot = BSLOT_WAVE + 2 * wi + (BM ? 1 : 0);
+  const int slot = BSLOT_WAVE + 2 * wi + (ACC == ACC_BITMAP ? 1 : 0);
   const unsigned nt = 64 * PIPE_WAVES_PER_BLOCK;
   switch (wi) {
-    case 0: k_batch_wave<1, NUM, V, BM><<<blocks, nt, lds, s>>>(b, a, slot); break;
-    case 1: k_batch_wave<2, NUM, V, BM><<<blocks, nt, lds, s>>>(b, a, slot); break;
-    case 2: k_batch_wave<3, NUM, V, BM><<<blocks, nt, lds, s>>>(b, a, slot); break;
-    case 3: k_batch_wave<4, NUM, V, BM><<<blocks, nt, lds, s>>>(b, a, slot); break;
-    case 4: k_batch_wave<5, NUM, V, BM><<<blocks, nt, lds, s>>>(b, a, slot); break;
-    case 5: k_batch_wave<6, NUM, V, BM><<<blocks, nt, lds, s>>>(b, a, slot); break;
-    case 6: k_batch_wave<8, NUM, V, BM><<<blocks, nt, lds, s>>>(b, a, slot); break;
-    case 7: k_batch_wave<10, NUM, V, BM><<<blocks, nt, lds, s>>>(b, a, slot); break;
-    case 8: k_batch_wave<12, NUM, V, BM><<<blocks, nt, lds, s>>>(b, a, slot); break;
-    default: k_batch_wave<16, NUM, V, BM><<<blocks, nt, lds, s>>>(b, a, slot); break;
+    case 0: k_batch_wave<1, NUM, V, ACC><<<blocks, nt, lds, s>>>(b, a, slot); break;
+    case 1: k_batch_wave<2, NUM, V, ACC><<<blocks, nt, lds, s>>>(b, a, slot); break;
+    case 2: k_batch_wave<3, NUM, V, ACC><<<blocks, nt, lds, s>>>(b, a, slot); break;
+    case 3: k_batch_wave<4, NUM, V, ACC><<<blocks, nt, lds, s>>>(b, a, slot); break;
+    case 4: k_batch_wave<5, NUM, V, ACC><<<blocks, nt, lds, s>>>(b, a, slot); break;
+    case 5: k_batch_wave<6, NUM, V, ACC><<<blocks, nt, lds, s>>>(b, a, slot); break;
+    case 6: k_batch_wave<8, NUM, V, ACC><<<blocks, nt, lds, s>>>(b, a, slot); break;
+    case 7: k_batch_wave<10, NUM, V, ACC><<<blocks, nt, lds, s>>>(b, a, slot); break;
+    case 8: k_batch_wave<12, NUM, V, ACC><<<blocks, nt, lds, s>>>(b, a, slot); break;
+    default: k_batch_wave<16, NUM, V, ACC><<<blocks, nt, lds, s>>>(b, a, slot); break;
   }
+}
+
+template <bool NUM, typename V>
+static void launch_bw_any(int wi, bool bm, const BatchArgs& b, const KArgs& a, unsigned blocks, size_t lds,
+                          hipStream_t s) {
+  if (bm) launch_bw<NUM, V, ACC_BITMAP>(wi, b, a, blocks, lds, s);
+  else if (b.accum_mode != 1) launch_bw<NUM, V, ACC_RANKED>(wi, b, a, blocks, lds, s);
+  else launch_bw<NUM, V, ACC_HASH>(wi, b, a, blocks, lds, s);
 }
 
 void launch_batch_wave(int wi, bool numeric, bool f64, bool bm, const BatchArgs& b, const KArgs& a, unsigned blocks,
                        size_t lds, hipStream_t s) {
-  if (!numeric) {
-    if (bm) launch_bw<false, float, true>(wi, b, a, blocks, lds, s);
-    else launch_bw<false, float, false>(wi, b, a, blocks, lds, s);
-  } else if (f64) {
-    if (bm) launch_bw<true, double, true>(wi, b, a, blocks, lds, s);
-    else launch_bw<true, double, false>(wi, b, a, blocks, lds, s);
-  } else {
-    if (bm) launch_bw<true, float, true>(wi, b, a, blocks, lds, s);
-    else launch_bw<true, float, false>(wi, b, a, blocks, lds, s);
-  }
+  if (!numeric) launch_bw_any<false, float>(wi, bm, b, a, blocks, lds, s);
+  else if (f64) launch_bw_any<true, double>(wi, bm, b, a, blocks, lds, s);
+  else launch_bw_any<true, float>(wi, bm, b, a, blocks, lds, s);
 }
 
 }  // namespace spk

@@ -44,6 +44,14 @@ constexpr int PIPE_WAVES_PER_BLOCK = 4;  // pipelined wave kernels: the wavefron
                                          // the CU L1 for neighbouring columns
 constexpr int PLAN_THREADS = 256;
 
+// Accumulators of the pipelined wave kernels (wave_device.h).
+enum Acc : int { ACC_HASH = 0, ACC_BITMAP = 1, ACC_RANKED = 2 };
+// Rows of 8192 bits of the ranked bitmap's top level, and the tallest matrix it serves
+// in two levels (with one row more it takes three; one of the two needs the largest
+// LDS slice).
+constexpr int RK_TOP_ROWS = 4;
+constexpr int RANKED_WORST_M = 8192 * 64 * RK_TOP_ROWS;
+
 struct PlanParams {
   int m, n, k;
   int wave_max;     // largest u_j of the wave bins
@@ -96,7 +104,8 @@ struct KArgs {
   // LDS layout (bytes, per wave for the wave kernels, per block for the workgroup kernels)
   int ts_max;             // table slots available
   int off_P, off_adj, off_adjv, off_hist, off_match, off_mark, slice_bytes;
-  int bm_nq;              // wave bitmap mode: bitmap rows of 256 words (0 = hash mode)
+  int bm_nq;              // wave bitmap: bitmap rows of 256 words
+  int rk_nq, rk_shift;    // wave ranked bitmap: rows of 256 words and log2 block rows of the top level
   int off_bm, off_pre, off_bvals, off_brows;
   // workgroup units: units at most wg_span_max rows wide go to the bitmap kernel (the
   // hash kernel skips them); wg_cap = its staging capacity in output entries
@@ -126,9 +135,11 @@ int bin_units_per_block(int bin);
 hipError_t launch_hash(int bin, bool numeric, bool f64, const KArgs& a, const int* d_list, int nunits,
                        hipStream_t s);
 const char* hash_kernel_name(int bin, bool numeric);
-// Pipelined wave-bin kernels (wave_kernels.hip): k <= 64 and numeric load factor 1/2.
-bool wave_pipe_ok(int k, int alpha_num_q);
-void lds_layout_pipe(int bin, bool numeric, int vbytes, int ts_max, int bm_nq, KArgs& a);
+// Pipelined wave-bin kernels (wave_kernels.hip): numeric load factor 1/2, and k <= 64
+// with hash tables, k <= 128 without.
+bool wave_pipe_ok(int k, int alpha_num_q, int acc);
+// rows: bitmap rows of 8192 bits (ACC_BITMAP) or the matrix's height (ACC_RANKED)
+void lds_layout_pipe(int bin, bool numeric, int vbytes, int ts_max, int acc, int rows, int k, KArgs& a);
 // Workgroup bitmap kernel (bitmap_wg.hip): widest unit it takes (rows), LDS layout,
 // launch over a bin's units (G1, G2 or WIN).
 int bitmap_wg_span_max();
@@ -139,8 +150,9 @@ void lds_layout_bitmap_wg(bool numeric, int vbytes, int k, int span_max, int cap
 int bitmap_wg_regs(int bin);
 hipError_t launch_bitmap_wg(int bin, bool numeric, bool f64, const KArgs& a, const int* d_list, int nunits,
                             hipStream_t s);
-hipError_t launch_wave_pipe(int bin, bool numeric, bool f64, const KArgs& a, const int* d_list, int nunits,
-                            hipStream_t s);
+// upw (units per wavefront) is set by the launcher from the wavefronts that can be resident.
+hipError_t launch_wave_pipe(int bin, bool numeric, bool f64, int acc, const KArgs& a, const int* d_list, int nunits,
+                            int n_cu, hipStream_t s);
 int max_lds_bytes();
 
 // Sets the calling thread's spkadd_last_error message and returns st (spkadd.cpp).

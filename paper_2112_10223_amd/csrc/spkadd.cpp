@@ -408,7 +408,7 @@ int ktop_of(int k) {
   return t;
 }
 
-bool layout_bin(const spkadd_plan_s* p, int b, bool numeric, KArgs& a);
+bool layout_bin(const spkadd_plan_s* p, int b, bool numeric, KArgs& a, int& acc);
 bool wg_bitmap_bin(const spkadd_plan_s* p, int b);
 void wg_bitmap_layout(const spkadd_plan_s* p, int b, bool numeric, KArgs& a, bool worst);
 
@@ -419,7 +419,8 @@ spkadd_status check_lds(spkadd_plan_s* p) {
     if (cnt == 0) continue;
     for (int numeric = 0; numeric < 2; ++numeric) {
       KArgs a{};
-      const bool pipe = layout_bin(p, b, numeric != 0, a);
+      int acc = 0;
+      const bool pipe = layout_bin(p, b, numeric != 0, a, acc);
       long long bytes = (long long)a.slice_bytes * (pipe ? PIPE_WAVES_PER_BLOCK : bin_units_per_block(b));
       if (wg_bitmap_bin(p, b)) {
         KArgs ab{};
@@ -778,23 +779,34 @@ spkadd_status build_windows_unsorted(spkadd_plan_s* p, hipStream_t s) {
 
 bool is_wave(int b) { return b >= BIN_W1 && b <= BIN_W16; }
 
-// Bitmap rows (of 256 words) for a wave bin, or 0 for hash tables.
-int bitmap_rows(const spkadd_plan_s* p, int b) {
-  if (!is_wave(b) || p->opts.accum_mode == SPKADD_ACCUM_HASH) return 0;
-  const long long nq = ((long long)p->m + 8191) / 8192;
-  if (nq < 1 || nq > 16) return 0;
-  if (p->opts.accum_mode == SPKADD_ACCUM_BITMAP) return (int)nq;
+// The accumulator of a wave bin: hash tables where asked for (accum_mode, or the
+// degenerate-hash test hook), the bitmap over all rows (nq rows of 256 words) where the
+// columns are dense enough for it, else the ranked bitmap.
+int wave_acc(const spkadd_plan_s* p, int b, int& nq) {
+  nq = 0;
+  if (p->opts.accum_mode == SPKADD_ACCUM_HASH) return ACC_HASH;
+  const long long rows = ((long long)p->m + 8191) / 8192;
   const float ratio = p->opts.bitmap_ratio > 0 ? p->opts.bitmap_ratio : 1.0f;
-  return nq <= ratio * wave_bin_E(b) ? (int)nq : 0;
+  if (rows >= 1 && rows <= 16 && (p->opts.accum_mode == SPKADD_ACCUM_BITMAP || rows <= ratio * wave_bin_E(b))) {
+    nq = (int)rows;
+    return ACC_BITMAP;
+  }
+  return p->opts.hash_mode != 0 ? ACC_HASH : ACC_RANKED;
 }
 
-// LDS layout of bin b for a phase; returns whether the pipelined wave kernel runs it.
-bool layout_bin(const spkadd_plan_s* p, int b, bool numeric, KArgs& a) {
+// LDS layout of bin b for a phase; returns whether the pipelined wave kernel runs it
+// (then with accumulator acc).
+bool layout_bin(const spkadd_plan_s* p, int b, bool numeric, KArgs& a, int& acc) {
   const int vb = p->dtype == SPKADD_F64 ? 8 : 4;
   const int ts = numeric ? p->ts_num[b] : p->ts_sym[b];
-  if (is_wave(b) && wave_pipe_ok(p->k, p->alpha_num_q)) {
-    lds_layout_pipe(b, numeric, vb, ts, bitmap_rows(p, b), a);
-    return true;
+  acc = ACC_HASH;
+  if (is_wave(b)) {
+    int nq = 0;
+    acc = wave_acc(p, b, nq);
+    if (wave_pipe_ok(p->k, p->alpha_num_q, acc)) {
+      lds_layout_pipe(b, numeric, vb, ts, acc, acc == ACC_RANKED ? p->m : nq, p->k, a);
+      return true;
+    }
   }
   lds_layout(b, numeric, vb, p->k, ts, a);
   a.bm_nq = 0;
@@ -853,44 +865,38 @@ hipError_t launch_bin(spkadd_plan_s* p, int b, bool numeric, KArgs& a_in, hipStr
     wg_bitmap_layout(p, b, numeric, ab);
     hipError_t e = launch_bitmap_wg(b, numeric, f64, ab, list, cnt, s);
     if (e != hipSuccess || b != BIN_WIN || p->max_span <= ab.wg_span_max) return e;
-    layout_bin(p, b, numeric, a);
+    int acc = 0;
+    layout_bin(p, b, numeric, a, acc);
     a.wg_span_max = ab.wg_span_max;
     TraceScope t(p, numeric ? "num_window_wide" : "sym_window_wide", s, numeric);
     return launch_hash(b, numeric, f64, a, list, cnt, s);
   }
-  if (layout_bin(p, b, numeric, a)) {
-    // resident wavefronts per CU: LDS-bound, at most 16 (four per SIMD)
-    const int block_lds = a.slice_bytes * PIPE_WAVES_PER_BLOCK;
-    int bpc = max_lds_bytes() / block_lds;
-    if (bpc > 16 / PIPE_WAVES_PER_BLOCK) bpc = 16 / PIPE_WAVES_PER_BLOCK;
-    if (bpc < 1) bpc = 1;
-    const long long resident = (long long)p->n_cu * bpc * PIPE_WAVES_PER_BLOCK;
-    long long upw = (cnt + resident - 1) / resident;
-    a.upw = (int)(upw < 1 ? 1 : upw > 64 ? 64 : upw);
-    return launch_wave_pipe(b, numeric, f64, a, list, cnt, s);
-  }
+  int acc = 0;
+  if (layout_bin(p, b, numeric, a, acc)) return launch_wave_pipe(b, numeric, f64, acc, a, list, cnt, p->n_cu, s);
   return launch_hash(b, numeric, f64, a, list, cnt, s);
 }
 
 // The fused symbolic launch of the wave bins (wave_fused.hip): each bin's accumulator
 // and table size, the largest LDS slice of any wave bin, and the grid (resident
-// blocks).  False when some wave bin does not take the pipelined kernel or the
-// slices do not fit.
+// blocks, no more than the columns need).  False when some wave bin does not take the
+// pipelined kernel or the slices do not fit.
 bool wave_sym_fused_setup(const spkadd_plan_s* p, KArgs& a, WaveBinTable& t, unsigned& blocks) {
   int slice = 0;
   for (int wi = 0; wi < NWAVE_BINS; ++wi) {
     const int b = BIN_W1 + wi;
     KArgs x{};
-    if (!layout_bin(p, b, false, x)) return false;
+    if (!layout_bin(p, b, false, x, t.acc[wi])) return false;
     t.bm_nq[wi] = x.bm_nq;
     t.ts[wi] = p->ts_sym[b];
     if (x.slice_bytes > slice) slice = x.slice_bytes;
   }
   int bpc = max_lds_bytes() / (slice * PIPE_WAVES_PER_BLOCK);
-  if (bpc > 16 / PIPE_WAVES_PER_BLOCK) bpc = 16 / PIPE_WAVES_PER_BLOCK;  // four wavefronts per SIMD
+  if (bpc > SYM_FUSED_WAVES) bpc = SYM_FUSED_WAVES;  // (a workgroup puts one wavefront on each SIMD)
   if (bpc < 1) return false;
   a.slice_bytes = slice;
+  const int need = (p->n + PIPE_WAVES_PER_BLOCK - 1) / PIPE_WAVES_PER_BLOCK;
   blocks = (unsigned)(p->n_cu * bpc);
+  if (need > 0 && blocks > (unsigned)need) blocks = (unsigned)need;
   return true;
 }
 
@@ -1085,7 +1091,7 @@ spkadd_status plan_build(spkadd_plan_s* p, int32_t m, int32_t n, int32_t k, cons
   // inputs (the validation errors are the plan's), when an input has no row array,
   // in region mode (pageable summaries) and when the wave bins do not take the
   // pipelined kernels.
-  bool defer = !p->region_mode && !(o.flags & SPKADD_FLAG_VALIDATE) && wave_pipe_ok(k, p->alpha_num_q);
+  bool defer = !p->region_mode && !(o.flags & SPKADD_FLAG_VALIDATE);
   for (int i = 0; i < k && defer; ++i) defer = rowidx[i] != nullptr;
   if (defer) {
     KArgs fa{};

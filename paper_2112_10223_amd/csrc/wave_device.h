@@ -6,22 +6,54 @@
 // gw + 2G, ... (at most 64).  While it accumulates one column in LDS, the column
 // pointers of the column after next and the row (and value) loads of the next
 // column are already in flight.  Two register sets alternate, and the loop is
-// unrolled by two so that no register copy forces a wait.  Lane i < k keeps the
-// base pointers of input i for the whole run (k <= 64).
+// unrolled by two so that no register copy forces a wait.  Each lane keeps the base
+// pointers of its KC inputs for the whole run: input lane for k <= 64 (KC = 1), inputs
+// 2 lane and 2 lane + 1 for k <= 128 (KC = 2).
 //
-// Two accumulators, chosen per launch:
+// Three accumulators, chosen per launch:
 //  * hash (Algorithms 5 and 6): linear-probing LDS tables with compare-and-swap
 //    claims; the numeric table is then compacted, bucketed by the top 8 bits of
 //    (row - min row) and ranked inside each bucket, which sorts the column;
 //  * bitmap: one bit per row of the matrix in LDS (the dense accumulator of
 //    Algorithm 4 with the value array indexed by rank); the rank of a row among
 //    the set bits is its output position, so the column comes out sorted with no
-//    probing and no sort.
-// Either way the sorted column is written out coalesced.
+//    probing and no sort;
+//  * ranked bitmap: the same over the non-empty 64-row blocks only, for matrices too
+//    tall for a bitmap of all their rows.  A bitmap over the blocks gives each
+//    non-empty block its rank, and the row's bit is rank(block) * 64 + row % 64: at
+//    most 64 bits per entry, whatever the matrix's height.  It takes the place of the
+//    hash tables, whose probing, compaction, bucket sort and larger slices (9.8 KiB a
+//    wavefront at E = 8 against 5) cost more LDS instructions: 16 inputs of 1,000,003 x
+//    150,001 with 12 rows per column, fp32: numeric 502 -> 178 us, symbolic 252 -> 131.
+//    Where the bitmap over all rows fits, that one is faster (65,536 rows, E = 10:
+//    numeric 169 against 199 us, symbolic 72 against 126).
+// In every case the sorted column is written out coalesced.
 #pragma once
 #include "hash_common.h"
 
 namespace spk {
+
+// Levels of the ranked bitmap of an m-row matrix: the top level marks blocks of
+// 2^shift rows (shift a multiple of 6) in nq rows of 8192 bits, at most RK_TOP_ROWS.
+// The levels below it hold at most 64 sub-blocks of each of a column's at most 64 E
+// non-empty blocks: rk_low_rows(E) rows of 8192 bits.
+__host__ __device__ constexpr int rk_low_rows(int E) { return (E + 1) / 2; }
+__host__ __device__ inline void rk_levels(int m, int& shift, int& nq) {
+  shift = 6;
+  while ((((long long)m + (1LL << shift) - 1) >> shift) > 8192LL * RK_TOP_ROWS) shift += 6;
+  const long long blocks = ((long long)m + (1LL << shift) - 1) >> shift;
+  nq = (int)((blocks + 8191) / 8192);
+  if (nq < 1) nq = 1;
+}
+
+// KiB of the symbolic segment table: start mask (at most 128 bytes) and row pointers.
+__host__ __device__ constexpr int sym_meta_rows(int KC) { return KC; }
+
+// Entries of a lane whose table lookups are in flight together.  Up to E = 10 all of
+// them; above, the registers they hold cost resident wavefronts (numeric bitmap, fp32,
+// E = 12 / 16: 141 / 179 registers in one group, three / two wavefronts per SIMD; 127 /
+// 161 in these groups, four / three).
+__host__ __device__ constexpr int lookup_group(int E) { return E <= 10 ? E : E == 12 ? 6 : 4; }
 
 // Entry addresses of one unit.  The non-empty segments (inputs with entries in the
 // column) are numbered in order, and each sets the bit of its start position in a
@@ -34,11 +66,16 @@ __device__ __forceinline__ void issue_unit_loads(const KArgs& a, unsigned char* 
                                                  int (&rows)[E], V (&vals)[E]) {
   const int lane = lane_id();
   const unsigned long long* sb = reinterpret_cast<const unsigned long long*>(base + a.off_mark);
-  long long ar[E], av[E];
   int before = -1;  // starts in earlier chunks, minus one
+  // (addresses of a few entries at a time: more of them would only cost registers)
+  constexpr int CH = lookup_group(E);
 #pragma unroll
-  for (int t = 0; t < E; ++t) {
-    const unsigned long long w = sb[t];
+  for (int t0 = 0; t0 < E; t0 += CH) {
+  if (t0 > 0) __builtin_amdgcn_sched_barrier(0);
+  long long ar[CH], av[CH];
+#pragma unroll
+  for (int t = 0; t < CH; ++t) {
+    const unsigned long long w = sb[t0 + t];
     // (the builtin returns int: go through unsigned so the low word is not sign-extended)
     const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(w >> 32));
     const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)w);
@@ -54,47 +91,63 @@ __device__ __forceinline__ void issue_unit_loads(const KArgs& a, unsigned char* 
     }
   }
 #pragma unroll
-  for (int t = 0; t < E; ++t) {
-    const int e = min(lane + 64 * t, u - 1);
-    rows[t] = gload<int>(ar[t] + 4LL * e);
-    if (NUM) vals[t] = gload<V>(av[t] + (long long)sizeof(V) * e);
+  for (int t = 0; t < CH; ++t) {
+    const int e = min(lane + 64 * (t0 + t), u - 1);
+    rows[t0 + t] = gload<int>(ar[t] + 4LL * e);
+    if (NUM) vals[t0 + t] = gload<V>(av[t] + (long long)sizeof(V) * e);
+  }
   }
 }
 
-// Column pointers of unit column j: lane i < k reads colptr_i[j], colptr_i[j+1];
-// lanes 0 and 1 also read colptr(B)[j], colptr(B)[j+1] for the numeric pass.
-// Lanes >= k hold the pointer of input k-1 and so repeat lane k-1's reads.
-template <bool NUM>
-__device__ __forceinline__ void issue_meta_loads(const KArgs& a, long long cpp, int j, int& s, int& e, int& cc) {
+// Column pointers of unit column j: a lane reads colptr_i[j], colptr_i[j+1] of its
+// inputs i; lanes 0 and 1 also read colptr(B)[j], colptr(B)[j+1] for the numeric pass.
+// Places past the last input hold its pointer and so repeat its reads.
+template <bool NUM, int KC>
+__device__ __forceinline__ void issue_meta_loads(const KArgs& a, const long long (&cpp)[KC], int j, int (&s)[KC],
+                                                 int (&e)[KC], int& cc) {
   const int lane = lane_id();
-  s = gload<int>(cpp + 4LL * j);
-  e = gload<int>(cpp + 4LL * (j + 1));
+#pragma unroll
+  for (int c = 0; c < KC; ++c) {
+    s[c] = gload<int>(cpp[c] + 4LL * j);
+    e[c] = gload<int>(cpp[c] + 4LL * (j + 1));
+  }
   if (NUM) cc = gload<int>((long long)(a.colptr_c + j + (lane & 1)));
 }
 
 // Segment table of a unit from its column pointers: the base pointers of the
 // non-empty segments, shifted so that entry index (position in the unit) addresses
 // them, in segment order, and the start mask.  Returns u.
-template <int E, bool NUM, typename V>
-__device__ __forceinline__ int build_unit_meta(const KArgs& a, unsigned char* base, long long rip, long long vap,
-                                               int s, int e, long long* adj) {
+template <int E, bool NUM, typename V, int KC>
+__device__ __forceinline__ int build_unit_meta(const KArgs& a, unsigned char* base, const long long (&rip)[KC],
+                                               const long long (&vap)[KC], const int (&s)[KC], const int (&e)[KC],
+                                               long long* adj) {
   const int lane = lane_id();
-  const int len = lane < a.k ? e - s : 0;
-  const int incl = wave_scan_add(len);
-  const int ex = incl - len;
-  const int ord = mbcnt(ballot(len > 0));
-  if (len > 0) {
-    // numeric: (rows, values) pointer pairs in the 16-byte slots of adj (its region
-    // holds 64 pairs there)
-    if constexpr (NUM)
-      reinterpret_cast<longlong2*>(adj)[ord] = make_longlong2(rip + 4LL * (s - ex), vap + (long long)sizeof(V) * (s - ex));
-    else
-      adj[ord] = rip + 4LL * (s - ex);
+  int len[KC], tot = 0, ord = 0;
+#pragma unroll
+  for (int c = 0; c < KC; ++c) {
+    len[c] = lane * KC + c < a.k ? e[c] - s[c] : 0;
+    tot += len[c];
+    ord += mbcnt(ballot(len[c] > 0));  // non-empty segments of the lanes below
   }
+  const int incl = wave_scan_add(tot);
   unsigned* sb = reinterpret_cast<unsigned*>(base + a.off_mark);
   if (lane < 2 * E) sb[lane] = 0u;
   wave_sync();
-  if (len > 0) atomicOr(&sb[ex >> 5], 1u << (ex & 31));
+  int ex = incl - tot;
+#pragma unroll
+  for (int c = 0; c < KC; ++c) {
+    if (len[c] > 0) {
+      // numeric: (rows, values) pointer pairs in the 16-byte slots of adj
+      if constexpr (NUM)
+        reinterpret_cast<longlong2*>(adj)[ord] =
+            make_longlong2(rip[c] + 4LL * (s[c] - ex), vap[c] + (long long)sizeof(V) * (s[c] - ex));
+      else
+        adj[ord] = rip[c] + 4LL * (s[c] - ex);
+      atomicOr(&sb[ex >> 5], 1u << (ex & 31));
+      ++ord;
+    }
+    ex += len[c];
+  }
   return readlane(incl, 63);
 }
 
@@ -311,57 +364,13 @@ __device__ __forceinline__ void num_unit(const KArgs& a, unsigned char* base, in
 // adds with compare-and-swap.
 // The bitmap holds bm_nq x 256 words (bm_nq x 8192 rows).
 // ---------------------------------------------------------------------------
-// Symbolic: OR the rows in; an OR that finds its bit clear counts a new row.  The
-// bitmap is all zero on entry (cleared at the start of the run) and is left all
-// zero: the words the unit touched are cleared again.
-template <int E>
-__device__ __forceinline__ int bm_sym_unit(const KArgs& a, unsigned char* base, int u, const int (&rows)[E]) {
+// Exclusive popcount prefix per pair of words of an nq x 256 word bitmap into pw32 (two
+// 16-bit prefixes per word; counts stay <= 1024).  Lane handles the 4 words (2 pairs)
+// of group q*64 + lane.  Two bitmap rows share one scan, one in each 16-bit half: no
+// partial sum exceeds the column's distinct rows, so the halves never carry into each
+// other.  Returns the number of set bits.
+__device__ __forceinline__ int bitmap_prefix(const uint4* bm4, unsigned* pw32, int nq) {
   const int lane = lane_id();
-  unsigned* bm = reinterpret_cast<unsigned*>(base + a.off_bm);
-  int newc = 0;
-  // lanes past the end hold a copy of the unit's last row and OR nothing
-#pragma unroll
-  for (int t = 0; t < E; ++t) {
-    const bool in = lane + 64 * t < u;
-    const unsigned bit = in ? 1u << (rows[t] & 31) : 0u;
-    const unsigned old = atomicOr(&bm[rows[t] >> 5], bit);
-    newc += (in && (old & bit) == 0) ? 1 : 0;
-  }
-  wave_sync();
-#pragma unroll
-  for (int t = 0; t < E; ++t) bm[rows[t] >> 5] = 0u;
-  wave_sync();
-  return wave_total_add(newc);
-}
-
-template <int E, typename V>
-__device__ __forceinline__ void bm_num_unit(const KArgs& a, unsigned char* base, int u, int cnt, int o0, bool live,
-                                            const int (&rows)[E], const V (&vals)[E]) {
-  const int lane = lane_id();
-  uint4* bm4 = reinterpret_cast<uint4*>(base + a.off_bm);
-  unsigned* bm = reinterpret_cast<unsigned*>(bm4);
-  unsigned short* pw = reinterpret_cast<unsigned short*>(base + a.off_pre);  // set bits below each word pair
-  V* bv = reinterpret_cast<V*>(base + a.off_bvals);  // may overlay the bitmap (used after the ranks)
-  // rows follow the 64 (E + 1) staged values (a.off_brows; a constant distance, so
-  // one address serves both)
-  int* br = reinterpret_cast<int*>(reinterpret_cast<unsigned char*>(bv) + 64 * (E + 1) * sizeof(V));
-  const int nq = a.bm_nq;
-  for (int q = 0; q < nq; ++q) bm4[q * 64 + lane] = make_uint4(0u, 0u, 0u, 0u);
-  wave_sync();
-  bool first[E];
-#pragma unroll
-  for (int t = 0; t < E; ++t) {
-    // lanes past the end hold a copy of the unit's last row and OR nothing
-    const bool in = lane + 64 * t < u;
-    const unsigned bit = in ? 1u << (rows[t] & 31) : 0u;
-    const unsigned old = atomicOr(&bm[rows[t] >> 5], bit);
-    first[t] = in && (old & bit) == 0;
-  }
-  wave_sync();
-  // exclusive popcount prefix per pair of words (ranks stay below 64 E <= 1024, so
-  // 16 bits hold them); lane handles the 4 words (2 pairs) of group q*64 + lane.
-  // Two bitmap rows share one scan, one in each 16-bit half: no partial sum exceeds
-  // the column's distinct rows (<= 1024), so the halves never carry into each other.
   int carry = 0;
   for (int q = 0; q < nq; q += 2) {
     const bool two = q + 1 < nq;
@@ -377,11 +386,151 @@ __device__ __forceinline__ void bm_num_unit(const KArgs& a, unsigned char* base,
     carry += tot & 0xffff;
     const int py = carry + (ex >> 16);
     carry += tot >> 16;
-    unsigned* pw32 = reinterpret_cast<unsigned*>(pw);
     pw32[q * 64 + lane] = (unsigned)px | ((unsigned)(px + x01) << 16);
     if (two) pw32[(q + 1) * 64 + lane] = (unsigned)py | ((unsigned)(py + y01) << 16);
   }
-  int c = carry;
+  return carry;
+}
+
+// Ranks of E set bits (bit numbers r): the set bits below each.  A group's lookups are
+// issued before the first is used (one LDS round trip).  (The word is
+// picked by masking, not by a select: a select between two array elements is turned
+// into an indexed scratch access.)
+// BLOCKS: the bits are those of the blocks r >> sh, and rk gets the block's rank in
+// place of its number (r and rk may be the same array).
+template <int E, bool BLOCKS = false>
+__device__ __forceinline__ void bitmap_ranks(const unsigned* bm, const unsigned short* pw, const int (&r)[E],
+                                             int (&rk)[E], int sh = 0) {
+  constexpr int CH = lookup_group(E);
+#pragma unroll
+  for (int t0 = 0; t0 < E; t0 += CH) {
+    if (t0 > 0) __builtin_amdgcn_sched_barrier(0);
+    unsigned plo[CH], phi[CH], pp[CH];
+#pragma unroll
+    for (int t = 0; t < CH; ++t) {
+      const int w = r[t0 + t] >> (BLOCKS ? sh + 5 : 5);
+      const uint2 pr = reinterpret_cast<const uint2*>(bm)[w >> 1];
+      plo[t] = pr.x;
+      phi[t] = pr.y;
+      pp[t] = pw[w >> 1];
+    }
+#pragma unroll
+    for (int t = 0; t < CH; ++t) {
+      const int x = BLOCKS ? r[t0 + t] >> sh : r[t0 + t];
+      const unsigned odd = 0u - (unsigned)((x >> 5) & 1);  // all ones for the second word of the pair
+      const unsigned word = plo[t] ^ ((plo[t] ^ phi[t]) & odd);
+      const int below = (int)pp[t] + (int)((unsigned)__popc(plo[t]) & odd) + __popc(word & ((1u << (x & 31)) - 1u));
+      rk[t0 + t] = BLOCKS ? (below << sh) | (r[t0 + t] & ((1 << sh) - 1)) : below;
+    }
+  }
+}
+
+// Ranked bitmap: the rows of a unit (lanes past the end hold a copy of its last row)
+// as bit numbers below 4096 E in the rows' order.  The top level marks the non-empty
+// blocks of 2^rk_shift rows; a block's rank replaces its number, which leaves at most
+// 64 E blocks.  While blocks are larger than 64 rows, they are divided into 64 again
+// and ranked again.  A row outside the matrix (invalid input) counts as its last.
+template <int E>
+__device__ __forceinline__ void rank_rows(const KArgs& a, unsigned char* base, const int (&rows)[E], int (&vr)[E]) {
+  const int lane = lane_id();
+  uint4* bm4 = reinterpret_cast<uint4*>(base);
+  unsigned* bm = reinterpret_cast<unsigned*>(base);
+  wave_sync();  // (the segment table read before shares the region)
+#pragma unroll
+  for (int t = 0; t < E; ++t) vr[t] = (int)min((unsigned)rows[t], (unsigned)(a.m - 1));
+  int nq = a.rk_nq;
+  for (int sh = a.rk_shift; sh > 0; sh -= 6) {  // (uniform)
+    unsigned short* pw = reinterpret_cast<unsigned short*>(base + nq * 1024);
+    for (int q = 0; q < nq; ++q) bm4[q * 64 + lane] = make_uint4(0u, 0u, 0u, 0u);
+    wave_sync();
+#pragma unroll
+    for (int t = 0; t < E; ++t) {
+      const int blk = vr[t] >> sh;
+      atomicOr(&bm[blk >> 5], 1u << (blk & 31));
+    }
+    wave_sync();
+    bitmap_prefix(bm4, reinterpret_cast<unsigned*>(pw), nq);
+    wave_sync();
+    bitmap_ranks<E, true>(bm, pw, vr, vr, sh);
+    wave_sync();
+    nq = rk_low_rows(E);
+  }
+}
+
+// ORs the rows' bits (vr) into the bitmap; returns the bits this lane found clear.
+// Lanes past the end hold a copy of the unit's last row: its bit is found clear once,
+// by whichever lane comes first, so they need no mask.
+template <int E>
+__device__ __forceinline__ int count_new(unsigned* bm, const int (&vr)[E]) {
+  int seen = 0;
+#pragma unroll
+  for (int t = 0; t < E; ++t)
+    seen += (int)__builtin_amdgcn_ubfe(atomicOr(&bm[vr[t] >> 5], 1u << (vr[t] & 31)), (unsigned)(vr[t] & 31), 1u);
+  return E - seen;
+}
+
+// Symbolic: OR the rows in; an OR that finds its bit clear counts a new row.  The
+// bitmap is all zero on entry (cleared at the start of the run) and is left all
+// zero: the words the unit touched are cleared again.
+template <int E>
+__device__ __forceinline__ int bm_sym_unit(const KArgs& a, unsigned char* base, const int (&rows)[E]) {
+  unsigned* bm = reinterpret_cast<unsigned*>(base + a.off_bm);
+  const int newc = count_new<E>(bm, rows);
+  wave_sync();
+#pragma unroll
+  for (int t = 0; t < E; ++t) bm[rows[t] >> 5] = 0u;
+  wave_sync();
+  return wave_total_add(newc);
+}
+
+// Symbolic over the ranked bitmap (cleared for every unit).
+template <int E>
+__device__ __forceinline__ int rk_sym_unit(const KArgs& a, unsigned char* base, const int (&rows)[E]) {
+  const int lane = lane_id();
+  uint4* bm4 = reinterpret_cast<uint4*>(base);
+  int vr[E];
+  rank_rows<E>(a, base, rows, vr);
+#pragma unroll
+  for (int q = 0; q < rk_low_rows(E); ++q) bm4[q * 64 + lane] = make_uint4(0u, 0u, 0u, 0u);
+  wave_sync();
+  const int newc = count_new<E>(reinterpret_cast<unsigned*>(base), vr);
+  wave_sync();
+  return wave_total_add(newc);
+}
+
+// RK: over the ranked bitmap, whose levels all start at the slice's base.
+template <int E, typename V, bool RK>
+__device__ __forceinline__ void bm_num_unit(const KArgs& a, unsigned char* base, int u, int cnt, int o0, bool live,
+                                            const int (&rows)[E], const V (&vals)[E]) {
+  const int lane = lane_id();
+  uint4* bm4 = reinterpret_cast<uint4*>(base + a.off_bm);
+  unsigned* bm = reinterpret_cast<unsigned*>(bm4);
+  unsigned short* pw = reinterpret_cast<unsigned short*>(base + a.off_pre);  // set bits below each word pair
+  V* bv = reinterpret_cast<V*>(base + a.off_bvals);  // may overlay the bitmap (used after the ranks)
+  // rows follow the 64 (E + 1) staged values (a.off_brows; a constant distance, so
+  // one address serves both)
+  int* br = reinterpret_cast<int*>(reinterpret_cast<unsigned char*>(bv) + 64 * (E + 1) * sizeof(V));
+  const int nq = RK ? rk_low_rows(E) : a.bm_nq;
+  int vr[E];  // the bits of the rows
+  if constexpr (RK) {
+    rank_rows<E>(a, base, rows, vr);
+  } else {
+#pragma unroll
+    for (int t = 0; t < E; ++t) vr[t] = rows[t];
+  }
+  for (int q = 0; q < nq; ++q) bm4[q * 64 + lane] = make_uint4(0u, 0u, 0u, 0u);
+  wave_sync();
+  bool first[E];
+#pragma unroll
+  for (int t = 0; t < E; ++t) {
+    // lanes past the end hold a copy of the unit's last row and OR nothing
+    const bool in = lane + 64 * t < u;
+    const unsigned bit = in ? 1u << (vr[t] & 31) : 0u;
+    const unsigned old = atomicOr(&bm[vr[t] >> 5], bit);
+    first[t] = in && (old & bit) == 0;
+  }
+  wave_sync();
+  int c = bitmap_prefix(bm4, reinterpret_cast<unsigned*>(pw), nq);
   if (c != cnt) {
     if (lane == 0) atomicOr(a.err, ERR_COUNT);
     c = 0;
@@ -390,26 +539,8 @@ __device__ __forceinline__ void bm_num_unit(const KArgs& a, unsigned char* base,
   wave_sync();
   // rank(row) = set bits below it = output position; the first entry of a row puts
   // the row and its value there, later entries of the row add their values
-  // every lookup is issued before the first is used (one LDS round trip, not E)
-  // (the word is picked by masking, not by a select: a select between two array
-  // elements is turned into an indexed scratch access)
   int rk[E];
-  unsigned plo[E], phi[E], pp[E];
-#pragma unroll
-  for (int t = 0; t < E; ++t) {
-    const int w = (lane + 64 * t < u ? rows[t] : 0) >> 5;
-    const uint2 pr = reinterpret_cast<const uint2*>(bm)[w >> 1];
-    plo[t] = pr.x;
-    phi[t] = pr.y;
-    pp[t] = pw[w >> 1];
-  }
-#pragma unroll
-  for (int t = 0; t < E; ++t) {
-    const int r = lane + 64 * t < u ? rows[t] : 0;
-    const unsigned odd = 0u - (unsigned)((r >> 5) & 1);  // all ones for the second word of the pair
-    const unsigned word = plo[t] ^ ((plo[t] ^ phi[t]) & odd);
-    rk[t] = (int)pp[t] + (int)((unsigned)__popc(plo[t]) & odd) + __popc(word & ((1u << (r & 31)) - 1u));
-  }
+  bitmap_ranks<E>(bm, pw, vr, rk);
   wave_sync();  // the bitmap is read for the last time above
   // entries that are not first write into per-lane sink slots 64 E + lane
 #pragma unroll
@@ -424,6 +555,7 @@ __device__ __forceinline__ void bm_num_unit(const KArgs& a, unsigned char* base,
     if (lane + 64 * t < u && !first[t]) lds_add_cas<V>(&bv[rk[t]], vals[t]);
   wave_sync();
   write_column<E, V>(a, o0, c, br, bv);
+  if (RK) wave_sync();  // (the next unit's segment table shares the region)
 }
 
 // Marks the entry registers of a unit as needed here.  Called before the next
@@ -461,6 +593,17 @@ __device__ __forceinline__ void prime_stores(const KArgs& a) {
   }
 }
 
+// The symbolic bitmap shares its LDS with the segment table (mark and pointers, at the
+// slice's start), which is zeroed again once the unit's loads are issued.
+template <int KC>
+__device__ __forceinline__ void clear_meta(const KArgs& a, unsigned char* base) {
+  wave_sync();
+#pragma unroll
+  for (int q = 0; q < sym_meta_rows(KC); ++q)
+    reinterpret_cast<uint4*>(base)[q * 64 + lane_id()] = make_uint4(0u, 0u, 0u, 0u);
+  wave_sync();
+}
+
 template <int E, bool NUM, typename V>
 struct UnitRegs {
   int rows[E];
@@ -473,9 +616,10 @@ struct UnitRegs {
 // Steps t >= nu (the loop runs an even count) replay the wavefront's last unit with
 // its output sent to the write sink: every step runs the same instruction sequence
 // on a real column, so the compiler keeps the next unit's loads in flight.
-template <int E, bool NUM, typename V, bool BM>
+template <int E, bool NUM, typename V, int ACC, int KC>
 __device__ __forceinline__ void pipe_step(const KArgs& a, unsigned char* base, int t, int nu, int ucol,
-                                          long long cpp, long long rip, long long vap, int& ms, int& me, int& mc,
+                                          const long long (&cpp)[KC], const long long (&rip)[KC],
+                                          const long long (&vap)[KC], int (&ms)[KC], int (&me)[KC], int& mc,
                                           UnitRegs<E, NUM, V>& cur, UnitRegs<E, NUM, V>& nxt) {
   const int lane = lane_id();
   require_loaded<E, NUM, V>(cur.rows, cur.vals);
@@ -484,21 +628,22 @@ __device__ __forceinline__ void pipe_step(const KArgs& a, unsigned char* base, i
     // that writes them
     long long* adj = (long long*)(base + a.off_adj);
     nxt.j = t + 1 < nu ? readlane(ucol, t + 1) : -1;  // -1: a replay, no output
-    nxt.u = build_unit_meta<E, NUM, V>(a, base, rip, vap, ms, me, adj);
+    nxt.u = build_unit_meta<E, NUM, V, KC>(a, base, rip, vap, ms, me, adj);
     if (NUM) {
       nxt.o0 = readlane(mc, 0);
       nxt.cnt = readlane(mc, 1) - nxt.o0;
     }
-    issue_meta_loads<NUM>(a, cpp, readlane(ucol, min(t + 2, nu - 1)), ms, me, mc);
+    issue_meta_loads<NUM, KC>(a, cpp, readlane(ucol, min(t + 2, nu - 1)), ms, me, mc);
     wave_sync();
     issue_unit_loads<E, NUM, V>(a, base, adj, nxt.u, nxt.rows, nxt.vals);
+    if constexpr (!NUM && ACC == ACC_BITMAP) clear_meta<KC>(a, base);
   }
-  if constexpr (NUM && BM) {
-    bm_num_unit<E, V>(a, base, cur.u, cur.cnt, cur.o0, cur.j >= 0, cur.rows, cur.vals);
+  if constexpr (NUM && ACC != ACC_HASH) {
+    bm_num_unit<E, V, ACC == ACC_RANKED>(a, base, cur.u, cur.cnt, cur.o0, cur.j >= 0, cur.rows, cur.vals);
   } else if constexpr (NUM) {
     num_unit<E, V>(a, base, cur.u, cur.cnt, cur.o0, cur.j >= 0, cur.rows, cur.vals);
-  } else if constexpr (BM) {
-    const int cnt = bm_sym_unit<E>(a, base, cur.u, cur.rows);
+  } else if constexpr (ACC != ACC_HASH) {
+    const int cnt = ACC == ACC_RANKED ? rk_sym_unit<E>(a, base, cur.rows) : bm_sym_unit<E>(a, base, cur.rows);
     // one unconditional store instruction: lane 0 writes the count, the other
     // lanes (and replayed units) write into their write-sink slots
     const long long dmy = (long long)a.dummy + 2048 + 8LL * lane;
@@ -520,31 +665,36 @@ __device__ __forceinline__ void pipe_step(const KArgs& a, unsigned char* base, i
 
 // The pipeline over one wavefront's units: nu <= 64 unit column ids, lane t of
 // ucol holding unit t.  Every unit has entries (u > 0).
-template <int E, bool NUM, typename V, bool BM>
+template <int E, bool NUM, typename V, int ACC, int KC>
 __device__ __forceinline__ void run_pipe(const KArgs& a, unsigned char* base, int nu, int ucol) {
   const int lane = lane_id();
-  const int li = lane < a.k ? lane : a.k - 1;
-  const long long cpp = (long long)a.cp[li];
-  const long long rip = (long long)a.ri[li];
-  const long long vap = NUM ? (long long)a.va[li] : 0;
+  long long cpp[KC], rip[KC], vap[KC];
+#pragma unroll
+  for (int c = 0; c < KC; ++c) {
+    const int li = min(lane * KC + c, a.k - 1);
+    cpp[c] = (long long)a.cp[li];
+    rip[c] = (long long)a.ri[li];
+    vap[c] = NUM ? (long long)a.va[li] : 0;
+  }
 
   UnitRegs<E, NUM, V> A, B;
-  int ms = 0, me = 0, mc = 0;
+  int ms[KC], me[KC], mc = 0;
   // prologue: metadata and entry loads of unit 0, pointers of unit 1
-  issue_meta_loads<NUM>(a, cpp, readlane(ucol, 0), ms, me, mc);
+  issue_meta_loads<NUM, KC>(a, cpp, readlane(ucol, 0), ms, me, mc);
   {
     long long* adj = (long long*)(base + a.off_adj);
-    A.u = build_unit_meta<E, NUM, V>(a, base, rip, vap, ms, me, adj);
+    A.u = build_unit_meta<E, NUM, V, KC>(a, base, rip, vap, ms, me, adj);
     A.j = readlane(ucol, 0);
     if (NUM) {
       A.o0 = readlane(mc, 0);
       A.cnt = readlane(mc, 1) - A.o0;
     }
-    issue_meta_loads<NUM>(a, cpp, readlane(ucol, min(1, nu - 1)), ms, me, mc);
+    issue_meta_loads<NUM, KC>(a, cpp, readlane(ucol, min(1, nu - 1)), ms, me, mc);
     wave_sync();
     issue_unit_loads<E, NUM, V>(a, base, adj, A.u, A.rows, A.vals);
   }
-  if constexpr (!NUM && BM) {  // the symbolic bitmap starts all zero and stays so
+  if constexpr (!NUM && ACC == ACC_BITMAP) {  // the symbolic bitmap starts all zero and stays so
+    wave_sync();
     uint4* bm4 = reinterpret_cast<uint4*>(base + a.off_bm);
     for (int q = 0; q < a.bm_nq; ++q) bm4[q * 64 + lane] = make_uint4(0u, 0u, 0u, 0u);
     wave_sync();
@@ -552,17 +702,46 @@ __device__ __forceinline__ void run_pipe(const KArgs& a, unsigned char* base, in
   prime_stores<E, NUM, V>(a);
   const int steps = (nu + 1) & ~1;
   for (int t = 0; t < steps; t += 2) {
-    pipe_step<E, NUM, V, BM>(a, base, t, nu, ucol, cpp, rip, vap, ms, me, mc, A, B);
-    pipe_step<E, NUM, V, BM>(a, base, t + 1, nu, ucol, cpp, rip, vap, ms, me, mc, B, A);
+    pipe_step<E, NUM, V, ACC, KC>(a, base, t, nu, ucol, cpp, rip, vap, ms, me, mc, A, B);
+    pipe_step<E, NUM, V, ACC, KC>(a, base, t + 1, nu, ucol, cpp, rip, vap, ms, me, mc, B, A);
   }
 }
 
-// LDS layout of one wavefront's slice (bytes).  Region 1: the hash table (keys + 64
-// sink slots, then values and the 256-bucket histogram) or the bitmap (nq x 1 KiB)
-// with its pair prefix (nq x 256 B); for the numeric bitmap the rows and values
-// staged by rank overlay the bitmap when they fit in it.  Then the start mask
-// (E 64-bit words) and the segment pointer table.
-__host__ __device__ inline void pipe_layout(int E, bool numeric, int vbytes, int ts_max, int bm_nq, KArgs& a) {
+// LDS layout of one wavefront's slice (bytes) for accumulator acc, kc inputs per lane.
+// `rows` is the number of bitmap rows of 8192 bits (ACC_BITMAP) or the matrix's height
+// (ACC_RANKED).  Region 1: the hash table (keys + 64 sink slots, then values and the
+// 256-bucket histogram) or the bitmap (nq x 1 KiB) with its pair prefix (nq x 256 B);
+// for the numeric bitmap the rows and values staged by rank overlay the bitmap when
+// they fit in it.  Then the start mask (E 64-bit words) and the segment pointer table.
+// The ranked bitmap keeps nothing in LDS from one unit to the next, and the segment
+// table of the next unit is read (its loads issued) before this unit's accumulation
+// starts: its levels, staging and segment table all share one region.
+__host__ __device__ inline void pipe_layout(int E, bool numeric, int vbytes, int ts_max, int acc, int rows, int kc,
+                                            KArgs& a) {
+  const int adj_bytes = kc * 64 * (numeric ? 16 : 8);  // (rows, values) pointer pairs, or row pointers
+  const int mark_bytes = (8 * E + 15) & ~15;
+  a.ts_max = ts_max;
+  a.bm_nq = a.rk_nq = a.rk_shift = 0;
+  if (acc == ACC_RANKED) {
+    rk_levels(rows, a.rk_shift, a.rk_nq);
+    const int low = rk_low_rows(E);
+    a.off_bm = 0;
+    a.off_pre = low * 1024;
+    a.off_bvals = 0;
+    a.off_brows = 64 * (E + 1) * vbytes;
+    // (the symbolic pass needs no prefix of its last level)
+    int bytes = low * (numeric || a.rk_shift > 6 ? 1280 : 1024);
+    if (bytes < 1280 * a.rk_nq) bytes = 1280 * a.rk_nq;
+    const int staged = numeric ? 64 * (E + 1) * (vbytes + 4) : 0;
+    if (staged > bytes) bytes = staged;
+    a.off_mark = 0;
+    a.off_P = a.off_adj = a.off_adjv = mark_bytes;
+    if (mark_bytes + adj_bytes > bytes) bytes = mark_bytes + adj_bytes;
+    a.off_hist = 0;
+    a.slice_bytes = (bytes + 15) & ~15;
+    return;
+  }
+  const int bm_nq = acc == ACC_BITMAP ? rows : 0;
   int hash_bytes = (ts_max + 64) * 4;
   if (numeric) hash_bytes += (ts_max + 64) * vbytes + 272 * 4;
   int bm_bytes = 0;
@@ -578,27 +757,30 @@ __host__ __device__ inline void pipe_layout(int E, bool numeric, int vbytes, int
   int off = bm_nq > 0 ? bm_bytes : hash_bytes;
   off = (off + 15) & ~15;
   a.off_hist = ((ts_max + 64) * 4 + (ts_max + 64) * vbytes + 15) & ~15;  // used by the hash layout only
-  const int meta_bytes = ((8 * E + 15) & ~15) + (numeric ? 64 * 16 : 64 * 8);
-  if (numeric && bm_nq > 0 && meta_bytes <= bm_nq * 256) {
+  if (!numeric && bm_nq > 0) {
+    // the segment table is zeroed again after it is read, and shares the bitmap
+    a.off_mark = 0;
+    a.off_P = a.off_adj = a.off_adjv = mark_bytes;
+    const int meta = sym_meta_rows(kc) * 1024;
+    a.slice_bytes = off > meta ? off : meta;
+    return;
+  }
+  if (numeric && bm_nq > 0 && mark_bytes + adj_bytes <= bm_nq * 256) {
     // The start mask and the segment table of the next unit are read (its loads
     // issued) before this unit writes its prefix words, and written again only after
     // the unit's ranks are read: they share the prefix region.
     a.off_mark = a.off_pre;
-    a.off_P = a.off_adj = a.off_pre + ((8 * E + 15) & ~15);
+    a.off_P = a.off_adj = a.off_pre + mark_bytes;
     a.off_adjv = a.off_adj;
     a.slice_bytes = off;
-    a.ts_max = ts_max;
     return;
   }
   a.off_mark = off;
-  off += 8 * E;
-  off = (off + 15) & ~15;
-  a.off_P = off;
-  a.off_adj = off;  // numeric: 64 (rows, values) pointer pairs; symbolic: 64 row pointers
-  off += numeric ? 64 * 16 : 64 * 8;
+  off += mark_bytes;
+  a.off_P = a.off_adj = off;
   a.off_adjv = a.off_adj;  // (inside the pairs)
+  off += adj_bytes;
   a.slice_bytes = (off + 15) & ~15;
-  a.ts_max = ts_max;
 }
 
 }  // namespace spk

@@ -1,16 +1,22 @@
-// The symbolic pass of every wave bin in one launch (wave_fused.hip).  Not part of
+// The symbolic pass of the wave bins in one launch (wave_fused.hip).  Not part of
 // the public ABI.
 #pragma once
 #include "internal.h"
 
 namespace spk {
 
-// Per wave bin (index bin - BIN_W1): bitmap rows of 256 words (0: hash tables) and
-// symbolic table slots; the kernel derives each bin's LDS layout from them.
+// Per wave bin (index bin - BIN_W1): accumulator (ACC_*), bitmap rows of 256 words
+// (ACC_BITMAP) and symbolic table slots (ACC_HASH); the kernel derives each bin's LDS
+// layout from them.
 struct WaveBinTable {
+  int acc[NWAVE_BINS];
   int bm_nq[NWAVE_BINS];
   int ts[NWAVE_BINS];
 };
+
+// Wavefronts per SIMD of the fused launch: its registers are held to that (its longest
+// columns would take 137 and leave three).
+constexpr int SYM_FUSED_WAVES = 4;
 
 // Counts the distinct rows of every column of the wave bins.  The bins' column
 // lists and offsets are read on the device (d_list, d_binoff as the binning kernels

@@ -1,0 +1,10 @@
+// Wave-bin kernels: symbolic pass.
+#include "wave_kernels.h"
+
+namespace spk {
+
+hipError_t launch_pipe_sym(int bin, int acc, const KArgs& a, const int* list, int n, int n_cu, hipStream_t s) {
+  return launch_pipe_t<false, float>(bin, acc, a, list, n, n_cu, s);
+}
+
+}  // namespace spk

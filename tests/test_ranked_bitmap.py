@@ -1,0 +1,107 @@
+"""The ranked bitmap of the wave kernels (matrices too tall for a bitmap of all their
+rows) and two inputs per lane (64 < k <= 128), against the CPU oracle: rows bit-exact,
+integer values bit-exact, real values within max(k, t) * u * sum|a|."""
+import numpy as np
+import pytest
+import torch  # (before the library, which then shares its HIP runtime)
+
+import oracle
+import workloads
+from tests.gpu_util import assert_matches, note, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def _opts(**kw):
+    from paper_2112_10223_amd import binding
+    return binding.make_opts(**kw)
+
+
+def tall_batch(m, k, sizes, dtype, integers, seed):
+    """Columns of about the given input entries, drawn from a pool of rows (so that inputs
+    share rows) that holds the first and last rows of the matrix and of 64-row and
+    4096-row blocks."""
+    rng = np.random.default_rng(seed)
+    edges = np.array([0, 1, 31, 32, 63, 64, 65, 4095, 4096, m - 1, m - 2, m - 64, m - 65, m // 2], dtype=np.int64)
+    edges = edges[(edges >= 0) & (edges < m)]
+    rows, cps = [[] for _ in range(k)], np.zeros((k, len(sizes) + 1), np.int32)
+    for j, u in enumerate(sizes):
+        pool = np.unique(np.concatenate([edges, rng.integers(0, m, size=max(2, int(0.8 * u)))]))
+        if u == 0:
+            pool = pool[:0]
+        cnt = rng.multinomial(u, np.ones(k) / k)
+        for i in range(k):
+            r = np.sort(rng.choice(pool, size=min(int(cnt[i]), pool.shape[0]), replace=False)).astype(np.int32)
+            rows[i].append(r)
+            cps[i, j + 1] = cps[i, j] + r.shape[0]
+    rows = [np.concatenate(r) for r in rows]
+    if integers:
+        vals = [rng.integers(-3, 4, size=r.shape[0]).astype(dtype) for r in rows]
+    else:
+        vals = [rng.uniform(-1, 1, size=r.shape[0]).astype(dtype) for r in rows]
+    return workloads.CSCBatch(m, len(sizes), cps, rows, vals)
+
+
+SIZES = [0, 1, 2, 63, 64, 65, 128, 129, 190, 250, 257, 320, 321, 384, 500, 512, 513, 640, 641, 768, 900, 1023, 1024, 7,
+         0, 30]
+
+
+@pytest.mark.parametrize("m", [70000, 1 << 19, (1 << 19) + 1, 1 << 21, (1 << 21) + 1, 1 << 27, (1 << 27) + 1,
+                               (1 << 31) - 2])
+@pytest.mark.parametrize("k", [1, 7, 64, 65, 128])
+def test_levels(m, k):
+    dtype = np.float64 if (m + k) % 2 else np.float32
+    integers = k in (7, 65)
+    note(f"ranked bitmap m={m} k={k} {dtype.__name__} integers={integers}")
+    b = tall_batch(m, k, SIZES, dtype, integers, seed=m % 1000 + k)
+    got = run_gpu(b, _opts(), stats=True)
+    assert got[3]["n_wave_cols"] > 0
+    assert_matches(b, got, oracle.spkadd(b), exact_values=integers)
+
+
+@pytest.mark.parametrize("k", [65, 100, 127, 128, 129])
+@pytest.mark.parametrize("accum_mode", [0, 1, 2])
+def test_many_inputs(k, accum_mode):
+    """Bitmap, ranked bitmap and hash tables at the edges of two inputs per lane (k = 129
+    and hash tables above 64 take the unpipelined kernels)."""
+    for m in (3000, 60000, 200000):
+        note(f"many inputs k={k} m={m} accum_mode={accum_mode}")
+        b = tall_batch(m, k, SIZES, np.float32, True, seed=k)
+        assert_matches(b, run_gpu(b, _opts(accum_mode=accum_mode)), oracle.spkadd(b), exact_values=True)
+
+
+def test_more_columns_than_resident_wavefronts():
+    """Several units per wavefront (odd counts, replayed steps), one and two inputs per lane."""
+    for k, m, n in ((9, 300001, 20001), (70, 90001, 9001)):
+        note(f"ranked bitmap n={n} k={k}")
+        b = workloads.er(m, n, k, 3.0, seed=k, values="int32f")
+        assert_matches(b, run_gpu(b), oracle.spkadd(b), exact_values=True)
+
+
+def test_batched_requests_with_few_entries():
+    """Batched runs whose columns are too sparse for the bitmap, fused and one launch per
+    slot, requests of several heights in one run."""
+    from tests.gpu_util import to_device
+    from paper_2112_10223_amd import binding
+    reqs = [workloads.er(m, n, k, d, seed=m, values="int32f")
+            for m, n, k, d in ((65536, 300, 7, 3.0), (1 << 20, 500, 40, 9.0), (5000001, 200, 64, 14.0), (300, 50, 2, 1.0),
+                               ((1 << 21) + 1, 77, 20, 40.0))]
+    for fused in (0, -1):
+        note(f"batched ranked bitmap batch_fused_cols={fused}")
+        bt = binding.Batch(binding.SPKADD_F32, 8, 4000, 400, _opts(batch_fused_cols=fused))
+        args = []
+        for b in reqs:
+            cps, ris, vas = to_device(b)
+            args.append({"m": b.m, "colptrs": cps, "rowidxs": ris, "values": vas, "cap_c": b.nnz_in,
+                         "colptr_c": torch.zeros(b.n + 1, dtype=torch.int32, device="cuda:0"),
+                         "rowidx_c": torch.zeros(b.nnz_in, dtype=torch.int32, device="cuda:0"),
+                         "values_c": torch.zeros(b.nnz_in, dtype=torch.float32, device="cuda:0")})
+        for _ in range(2):
+            bt.run(args)
+            nnz, status = bt.results()
+        for b, q, z, st in zip(reqs, args, nnz, status):
+            assert st == binding.SPKADD_REQ_OK
+            got = (q["colptr_c"].cpu().numpy().astype(np.int64), q["rowidx_c"][:z].cpu().numpy(),
+                   q["values_c"][:z].cpu().numpy())
+            assert_matches(b, got, oracle.spkadd(b), exact_values=True)
+        bt.close()
