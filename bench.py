@@ -77,7 +77,8 @@ def kernel_of_column(u: np.ndarray, cap: int, wave_max: int = 1024, merge: bool 
 
 # kernel sources whose change makes a committed traffic summary stale, by trace-name prefix
 _KERNEL_SOURCES = {
-    "num_wave": ("hash_kernels.hip", "wave_kernels.hip", "wave_device.h", "hash_common.h", "device.h", "internal.h"),
+    "num_wave": ("hash_kernels.hip", "wave_kernels.hip", "wave_kernels.h", "wave_num_f32.hip", "wave_num_f64.hip",
+                 "wave_device.h", "hash_common.h", "device.h", "internal.h"),
     "num_window": ("bitmap_wg.hip", "bitmap_wg_device.h", "hash_kernels.hip", "hash_common.h", "device.h",
                    "internal.h"),
 }
