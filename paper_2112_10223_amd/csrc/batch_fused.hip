@@ -70,10 +70,9 @@ __global__ __launch_bounds__(64 * PIPE_WAVES_PER_BLOCK, NUM ? 2 : 4) void k_batc
 // Persistent, one launch per pass: workgroup w of W takes the columns w, w + W, ...
 // of the workgroup slot, each through the workgroup bitmap over its request's rows.
 template <int THREADS, bool NUM, typename V>
-__global__ __launch_bounds__(THREADS) void k_batch_wg(BatchArgs b, KArgs a) {
+__global__ __launch_bounds__(THREADS, (NUM && sizeof(V) == 8 ? 3 : 4)) void k_batch_wg(BatchArgs b, KArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ long long red[THREADS / 64 + 1];
-  __shared__ int info;
+  __shared__ int red[2 * (THREADS / 64) + 1];
   const int count = b.slotoff[BSLOTS + 1 + BSLOT_WG];
   const int off = b.slotoff[BSLOT_WG];
   for (int item = xcd_remap(blockIdx.x, gridDim.x); item < count; item += gridDim.x) {
@@ -88,15 +87,11 @@ __global__ __launch_bounds__(THREADS) void k_batch_wg(BatchArgs b, KArgs a) {
     ta.m = q.m;
     ta.n = q.n;
     ta.k = q.k;
-    int ktop = 0;  // largest power of two <= k - 1
-    while ((ktop << 1) <= q.k - 1) ktop = ktop ? ktop << 1 : 1;
-    ta.ktop = q.k > 1 ? ktop : 0;
     ta.colcnt = b.colcnt + q.col_base;
     ta.colptr_c = q.colptr_c;
     ta.out_r = q.out_r;
     ta.out_v = q.out_v;
-    bitmap_wg_unit<THREADS, BATCH_WG_U / THREADS, NUM, false, V>(ta, smem, red, &info, 0, g - q.col_base, 0, 0,
-                                                                q.m);
+    bitmap_wg_unit<THREADS, BATCH_WG_U / THREADS, NUM, false, V>(ta, smem, red, 0, g - q.col_base, 0, 0, q.m);
     __syncthreads();  // the next column rewrites the LDS this one may still read
   }
 }

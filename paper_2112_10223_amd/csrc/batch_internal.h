@@ -76,7 +76,7 @@ void launch_batch_wave(int wi, bool numeric, bool f64, bool bm, const BatchArgs&
 void launch_batch_fused(bool numeric, bool f64, const BatchArgs& b, const KArgs& a, unsigned blocks, size_t lds,
                         hipStream_t s);
 // The workgroup-sized columns of one pass; `a` holds the common fields and the LDS
-// layout (lds_layout_bitmap_wg for BATCH_WG_SPAN rows, BATCH_WG_U entries, k = 64).
+// layout (lds_layout_bitmap_wg for the batch's wg_max entries, BATCH_WG_SPAN rows, k = 64).
 void launch_batch_wg(bool numeric, bool f64, int threads, const BatchArgs& b, const KArgs& a, unsigned blocks,
                      hipStream_t s);
 // Blocks of the fused kernel resident per CU with `lds` bytes of LDS per block (0 if

@@ -211,7 +211,6 @@ __global__ __launch_bounds__(NT) void k_hash_wg(KArgs a, const int* __restrict__
   } else {
     j = list[unit];
   }
-  if (rhi - rlo <= a.wg_span_max) return;  // the bitmap kernel's unit (uniform; wg_span_max = 0: none)
   int* K = (int*)smem;
   V* Vt = (V*)(smem + a.ts_max * 4);
   int* P = (int*)(smem + a.off_P);
@@ -425,10 +424,10 @@ hipError_t launch_hash(int bin, bool numeric, bool f64, const KArgs& a, const in
 const char* hash_kernel_name(int bin, bool numeric) {
   static const char* sym[NBINS] = {"empty", "sym_wave_e1", "sym_wave_e2", "sym_wave_e3", "sym_wave_e4",
                                    "sym_wave_e5", "sym_wave_e6", "sym_wave_e8", "sym_wave_e10", "sym_wave_e12",
-                                   "sym_wave_e16", "sym_wg256", "sym_wg512", "sym_window"};
+                                   "sym_wave_e16", "sym_wg256", "sym_wg512", "sym_wg1024", "sym_window"};
   static const char* num[NBINS] = {"empty", "num_wave_e1", "num_wave_e2", "num_wave_e3", "num_wave_e4",
                                    "num_wave_e5", "num_wave_e6", "num_wave_e8", "num_wave_e10", "num_wave_e12",
-                                   "num_wave_e16", "num_wg256", "num_wg512", "num_window"};
+                                   "num_wave_e16", "num_wg256", "num_wg512", "num_wg1024", "num_window"};
   return (bin >= 0 && bin < NBINS) ? (numeric ? num[bin] : sym[bin]) : "?";
 }
 

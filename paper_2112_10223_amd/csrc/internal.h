@@ -12,13 +12,13 @@ namespace spk {
 // u_j = sum_i nnz(A_i(:,j)) (the per-column load measure of Section III-A).
 //   EMPTY      u_j = 0, nothing to do.
 //   W<E>       one wavefront per column, E entries per lane (u_j <= 64 E).
-//   G1, G2     one workgroup per column (256 / 512 threads).
+//   G1, G2, G3 one workgroup per column (256 / 512 / 1024 threads; G3 with bitmaps only).
 //   WIN        the column is cut into row windows (sliding hash, Section III-B);
 //              one workgroup per window.
 enum Bin : int {
   BIN_EMPTY = 0,
   BIN_W1, BIN_W2, BIN_W3, BIN_W4, BIN_W5, BIN_W6, BIN_W8, BIN_W10, BIN_W12, BIN_W16,
-  BIN_G1, BIN_G2,
+  BIN_G1, BIN_G2, BIN_G3,
   BIN_WIN,
   NBINS
 };
@@ -39,6 +39,8 @@ enum : int {
 // Threads of the workgroup bins.
 constexpr int G1_THREADS = 256;
 constexpr int G2_THREADS = 512;
+constexpr int G3_THREADS = 1024;
+constexpr int BITMAP_WG_EW = 8;  // entries per thread of the workgroup bitmap kernel
 constexpr int WAVES_PER_BLOCK = 4;   // wave bins (hash kernels): columns per 256-thread block
 constexpr int PIPE_WAVES_PER_BLOCK = 4;  // pipelined wave kernels: the wavefronts of a workgroup share
                                          // the CU L1 for neighbouring columns
@@ -57,11 +59,10 @@ struct PlanParams {
   int wave_max;     // largest u_j of the wave bins
   int g1_max;       // largest u_j of bin G1
   int cap_in;       // largest input count of a G2 column or a window
+  int g3_max;       // largest u_j of bin G3 (cap_in: none)
   int force_bin;    // -1 auto
   float win_fill;   // target window input count = cap_in * win_fill
   int unsorted_in;  // input columns may be unsorted (validation checks only the row range)
-  int win_min;      // fewest windows of a window column (each then at most the bitmap's rows)
-  int win_span;     // widest window left unsplit (the workgroup bitmap's rows; INT32_MAX without bitmaps)
 };
 
 // Summary written by the plan kernels; the host reads it from a pinned slot.
@@ -72,8 +73,6 @@ struct PlanSummary {
   int bin_count[NBINS];
   int n_windows;
   int pad;       // windows still to refine (one refinement level)
-  int max_span;  // widest window (rows) of the last level counted
-  int pad2;
 };
 
 // Arguments of the per-unit symbolic / numeric kernels.
@@ -103,15 +102,13 @@ struct KArgs {
   int upw;                // wave pipeline: units per wavefront
   // LDS layout (bytes, per wave for the wave kernels, per block for the workgroup kernels)
   int ts_max;             // table slots available
-  int off_P, off_adj, off_adjv, off_hist, off_match, off_mark, slice_bytes;
+  int off_P, off_adj, off_adjv, off_hist, off_match, off_mark, off_top, off_dpre, slice_bytes;
   int bm_nq;              // wave bitmap: bitmap rows of 256 words
   int rk_nq, rk_shift;    // wave ranked bitmap: rows of 256 words and log2 block rows of the top level
   int off_bm, off_pre, off_bvals, off_brows;
-  // workgroup units: units at most wg_span_max rows wide go to the bitmap kernel (the
-  // hash kernel skips them); wg_cap = its staging capacity in output entries
-  int wg_span_max, wg_cap;
-  int wg_overlay;         // the staging area may overlay the bitmap (ranks read first)
-  int wg_group;           // bitmap words per prefix entry (2 or 4)
+  // workgroup bitmap: largest range with one bit per row, bits of the top level, entries
+  // (staged output entries) of a unit
+  int wg_low_bits, wg_top_bits, wg_cap;
   int unsorted;           // numeric: 1 = write each column in table order (no sort)
 };
 
@@ -140,14 +137,11 @@ const char* hash_kernel_name(int bin, bool numeric);
 bool wave_pipe_ok(int k, int alpha_num_q, int acc);
 // rows: bitmap rows of 8192 bits (ACC_BITMAP) or the matrix's height (ACC_RANKED)
 void lds_layout_pipe(int bin, bool numeric, int vbytes, int ts_max, int acc, int rows, int k, KArgs& a);
-// Workgroup bitmap kernel (bitmap_wg.hip): widest unit it takes (rows), LDS layout,
-// launch over a bin's units (G1, G2 or WIN).
-int bitmap_wg_span_max();
-// one_max: a unit with at most this many entries keeps them all in registers (the
-// launch's threads x entries per thread); all_one: every unit of the launch does.
-void lds_layout_bitmap_wg(bool numeric, int vbytes, int k, int span_max, int cap, int one_max, bool all_one, int G,
-                          KArgs& a);
-int bitmap_wg_regs(int bin);
+// Workgroup bitmap kernel (bitmap_wg.hip): LDS layout for units of at most cap entries,
+// regs of them in registers, of at most span rows; threads per unit; launch over a bin's
+// units (G1, G2, G3 or WIN).
+void lds_layout_bitmap_wg(bool numeric, int vbytes, int k, int cap, int regs, int span, KArgs& a);
+int bitmap_wg_threads(int bin, int cap);
 hipError_t launch_bitmap_wg(int bin, bool numeric, bool f64, const KArgs& a, const int* d_list, int nunits,
                             hipStream_t s);
 // upw (units per wavefront) is set by the launcher from the wavefronts that can be resident.

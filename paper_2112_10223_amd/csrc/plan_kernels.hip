@@ -13,7 +13,7 @@ __device__ __forceinline__ int classify(long long u, const PlanParams& p) {
   if (p.force_bin == 2) return BIN_WIN;
   if (p.force_bin == 1) {
     if (u <= p.cap_in) return u <= p.g1_max ? BIN_G1 : BIN_G2;
-    return BIN_WIN;
+    return u <= p.g3_max ? BIN_G3 : BIN_WIN;
   }
   const int wave_limit = p.force_bin == 0 ? 1024 : p.wave_max;
   if (u <= wave_limit) {
@@ -22,7 +22,7 @@ __device__ __forceinline__ int classify(long long u, const PlanParams& p) {
          : e <= 6 ? BIN_W6 : e <= 8 ? BIN_W8 : e <= 10 ? BIN_W10 : e <= 12 ? BIN_W12 : BIN_W16;
   }
   if (u <= p.cap_in) return u <= p.g1_max ? BIN_G1 : BIN_G2;
-  return BIN_WIN;
+  return u <= p.g3_max ? BIN_G3 : BIN_WIN;
 }
 
 // u_j = sum_i nnz(A_i(:,j)), bin of j, per-block bin histogram, nnz_in.
@@ -217,8 +217,8 @@ __global__ __launch_bounds__(PLAN_THREADS) void k_bin_scatter(PlanParams p, cons
   }
 }
 
-// Initial number of windows of each window column: P = ceil(u / (cap_in * fill)), at
-// least win_min, clamped to [1, m]; exclusive scan into wfirst[0..n_wcols].  One block.
+// Initial number of windows of each window column: P = ceil(u / (cap_in * fill)),
+// clamped to [1, m]; exclusive scan into wfirst[0..n_wcols].  One block.
 __global__ __launch_bounds__(1024) void k_win_scan(PlanParams p, const int* __restrict__ list,
                                                    const int* __restrict__ binoff, const int* __restrict__ u,
                                                    int* __restrict__ wfirst, PlanSummary* __restrict__ sum) {
@@ -233,7 +233,6 @@ __global__ __launch_bounds__(1024) void k_win_scan(PlanParams p, const int* __re
     if (c < n_wcols) {
       const int uj = u[wcols[c]];
       pc = (long long)ceil((double)uj / (target > 1.0 ? target : 1.0));
-      if (pc < p.win_min) pc = p.win_min;
       if (pc < 1) pc = 1;
       if (pc > p.m) pc = p.m;
     }
@@ -672,7 +671,7 @@ __global__ __launch_bounds__(256) void k_win_count(PlanParams p, int n_windows, 
                                                    PlanSummary* __restrict__ sum) {
   const int lane = lane_id();
   const int nwave = (int)gridDim.x * 4;
-  int wmax = 0, nref = 0;  // over this wavefront's windows
+  int nref = 0;  // over this wavefront's windows
   for (int w = blockIdx.x * 4 + (threadIdx.x >> 6); w < n_windows; w += nwave) {
     const int b = w + win_c[w];
     long long cnt = 0;
@@ -686,17 +685,12 @@ __global__ __launch_bounds__(256) void k_win_count(PlanParams p, int n_windows, 
       cnt = cntin[w];  // counted by histogram (unsorted input)
     }
     const int width = brow[b + 1] - brow[b];
-    wmax = max(wmax, width);
     int pieces = 1;
     long long qq = 1;
     if (cnt > p.cap_in && width > p.cap_in) {
       const double target = (double)p.cap_in * (double)p.win_fill;
       qq = (long long)ceil((double)cnt / (target > 1.0 ? target : 1.0));
       if (qq < 2) qq = 2;
-    }
-    if (width > p.win_span) {  // wider than the workgroup bitmap: equal pieces that fit it
-      const long long qw = ((long long)width + p.win_span - 1) / p.win_span;
-      if (qw > qq) qq = qw;
     }
     if (qq > 1) {
       if (qq > width) qq = width;
@@ -708,26 +702,22 @@ __global__ __launch_bounds__(256) void k_win_count(PlanParams p, int n_windows, 
       q[w] = pieces;
     }
   }
-  // the widest window and the windows still to refine: one atomic of each per
-  // wavefront (one per window would all go to the same two words)
-  if (lane == 0) {
-    if (wmax > 0) atomicMax(&sum->max_span, wmax);
-    if (nref) atomicAdd(&sum->pad, nref);
-  }
+  // the windows still to refine: one atomic per wavefront that has any (one per window
+  // would all go to the same word)
+  if (lane == 0 && nref) atomicAdd(&sum->pad, nref);
 }
 
 // One refinement level: window w becomes q[w] row ranges.  newfirst is the exclusive
-// scan of q.  With the boundary positions of sorted inputs (bpos_old) a window no wider
-// than the workgroup bitmap is cut at row quantiles of its longest input within the
-// window (as the first windows are, so the pieces hold about equal entries and one
-// level mostly suffices on skewed rows); otherwise, and for a window cut for its
-// width, into equal row ranges.  The cuts are forced strictly increasing inside the
+// scan of q.  With the boundary positions of sorted inputs (bpos_old) a window is cut at
+// row quantiles of its longest input within the window (as the first windows are, so
+// the pieces hold about equal entries and one level mostly suffices on skewed rows);
+// otherwise into equal row ranges.  The cuts are forced strictly increasing inside the
 // window, so any rows give valid windows.
 __global__ __launch_bounds__(256) void k_win_refine_fill(int n_windows, int n_wcols, const int* __restrict__ win_c,
                                                          const int* __restrict__ wfirst_old,
                                                          const int* __restrict__ q,
                                                          const int* __restrict__ newfirst,
-                                                         const int* __restrict__ brow_old, int k, int win_span,
+                                                         const int* __restrict__ brow_old, int k,
                                                          const int* const* __restrict__ ri,
                                                          const int* __restrict__ bpos_old,
                                                          int* __restrict__ win_c_new, int* __restrict__ brow_new,
@@ -740,7 +730,7 @@ __global__ __launch_bounds__(256) void k_win_refine_fill(int n_windows, int n_wc
     const int rlo = brow_old[w + c], rhi = brow_old[w + c + 1];
     // the window's longest input (lowest index among equals)
     int best_len = 0, best_lo = 0, best_i = 0;
-    if (bpos_old && pieces > 1 && rhi - rlo <= win_span) {
+    if (bpos_old && pieces > 1) {
       const int* lo = bpos_old + (long long)(w + c) * k;
       const int* hi = lo + k;
       for (int i = 0; i < k; ++i) {
@@ -1040,7 +1030,7 @@ void launch_win_refine_fill(const PlanParams& p, int n_windows, int n_wcols, con
                             int* d_bcol_new, int* d_bpar, int* d_bpiece, int* d_wfirst_new, hipStream_t s) {
   const int work = (n_windows > n_wcols + 1 ? n_windows : n_wcols + 1);
   k_win_refine_fill<<<grid_for(work, 256), 256, 0, s>>>(n_windows, n_wcols, d_win_c, d_wfirst_old, d_q,
-                                                        d_newfirst, d_brow_old, p.k, p.win_span, d_ri, d_bpos_old,
+                                                        d_newfirst, d_brow_old, p.k, d_ri, d_bpos_old,
                                                         d_win_c_new, d_brow_new, d_bcol_new, d_bpar, d_bpiece,
                                                         d_wfirst_new);
 }

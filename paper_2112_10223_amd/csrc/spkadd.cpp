@@ -275,7 +275,6 @@ struct spkadd_plan_s {
   int binoff[NBINS + 1] = {0};
   // windows
   int n_wcols = 0, n_windows = 0, levels = 0;
-  int max_span = 0;  // widest window (rows)
   int* d_wfirst = nullptr;
   int* d_win_c = nullptr;
   int* d_brow = nullptr;
@@ -393,8 +392,16 @@ void clear_trace(spkadd_plan_s* p) {
   p->trace.clear();
 }
 
-constexpr int kDefaultCapF32 = 3072;
-constexpr int kDefaultCapF64 = 2048;
+// Window capacity: with bitmaps the most entries at which four workgroups of 512 threads
+// share a CU's LDS (4096 is also what their registers hold), with hash tables what two
+// share it at.  The ordered pass keeps the smaller ones, which its tables are sized by.
+constexpr int kDefaultCapF32 = 4096, kDefaultCapF64 = 3072;
+constexpr int kHashCapF32 = 3072, kHashCapF64 = 2048;
+// Sums of fewer columns than this keep the smaller capacities too: one workgroup per
+// column would leave most CUs idle, the row windows of a column are shared out.
+constexpr int kManyCols = 64;
+// Longest column of one workgroup of 1024 threads (two share a CU's LDS).
+constexpr int kG3MaxF32 = 8192, kG3MaxF64 = 6144;
 constexpr int kMaxCap = 8192;
 constexpr float kDefaultAlphaSym = 0.5f;
 constexpr float kDefaultAlphaNum = 0.5f;
@@ -410,7 +417,7 @@ int ktop_of(int k) {
 
 bool layout_bin(const spkadd_plan_s* p, int b, bool numeric, KArgs& a, int& acc);
 bool wg_bitmap_bin(const spkadd_plan_s* p, int b);
-void wg_bitmap_layout(const spkadd_plan_s* p, int b, bool numeric, KArgs& a, bool worst);
+void wg_bitmap_layout(const spkadd_plan_s* p, int b, bool numeric, KArgs& a);
 
 spkadd_status check_lds(spkadd_plan_s* p) {
   const int lmax = max_lds_bytes();
@@ -423,9 +430,8 @@ spkadd_status check_lds(spkadd_plan_s* p) {
       const bool pipe = layout_bin(p, b, numeric != 0, a, acc);
       long long bytes = (long long)a.slice_bytes * (pipe ? PIPE_WAVES_PER_BLOCK : bin_units_per_block(b));
       if (wg_bitmap_bin(p, b)) {
-        KArgs ab{};
-        wg_bitmap_layout(p, b, numeric != 0, ab, true);
-        if (ab.slice_bytes > bytes) bytes = ab.slice_bytes;
+        wg_bitmap_layout(p, b, numeric != 0, a);
+        bytes = a.slice_bytes;
       }
       if (bytes > lmax)
         return set_error(SPKADD_ERR_UNSUPPORTED,
@@ -566,7 +572,7 @@ spkadd_status build_windows(spkadd_plan_s* p, hipStream_t s) {
   p->release(d_chcol, s);
   p->release(d_bpos_t, s);
   p->release(d_wlin, s);
-  HIP_TRY(hipMemsetAsync(&p->d_sum->pad, 0, 2 * sizeof(int), s));  // pad and max_span
+  HIP_TRY(hipMemsetAsync(&p->d_sum->pad, 0, sizeof(int), s));
   {
     TraceScope t(p, "win_count", s);
     launch_win_count(p->pp, W, p->d_win_c, p->d_brow, p->d_bpos, p->d_cntin, d_q, p->d_sum, s);
@@ -606,7 +612,7 @@ spkadd_status build_windows(spkadd_plan_s* p, hipStream_t s) {
       TraceScope t(p, "win_refine_search", s);
       launch_win_refine_search(p->pp, p->d_ri, W2 + nwc, bcol2, brow2, bpar, bpiece, d_q, p->d_bpos, bpos2, s);
     }
-    HIP_TRY(hipMemsetAsync(&p->d_sum->pad, 0, 2 * sizeof(int), s));  // pad and max_span
+    HIP_TRY(hipMemsetAsync(&p->d_sum->pad, 0, sizeof(int), s));
     {
       TraceScope t(p, "win_count", s);
       launch_win_count(p->pp, W2, win_c2, brow2, bpos2, cntin2, q2, p->d_sum, s);
@@ -636,7 +642,6 @@ spkadd_status build_windows(spkadd_plan_s* p, hipStream_t s) {
   }
   p->release(d_q, s);
   p->n_windows = W;
-  p->max_span = p->h_sum->max_span;  // of the last level counted (the final windows)
   if ((st = p->alloc(&p->d_win_cnt, W, s))) return st;
   if ((st = p->alloc(&p->d_win_off, W, s))) return st;
   if ((st = p->alloc(&p->d_wrec, W, s))) return st;
@@ -691,7 +696,7 @@ spkadd_status build_windows_unsorted(spkadd_plan_s* p, hipStream_t s) {
       launch_uwin_hist(p->pp, p->d_cp, p->d_ri, (int)nchunks, wcols, p->d_wfirst, p->d_brow, d_chfirst, d_chcol,
                        p->d_cntin, s);
     }
-    HIP_TRY(hipMemsetAsync(&p->d_sum->pad, 0, 2 * sizeof(int), s));  // pad and max_span
+    HIP_TRY(hipMemsetAsync(&p->d_sum->pad, 0, sizeof(int), s));
     {
       TraceScope t(p, "win_count", s);
       launch_win_count(p->pp, W, p->d_win_c, p->d_brow, nullptr, p->d_cntin, d_q, p->d_sum, s);
@@ -736,7 +741,6 @@ spkadd_status build_windows_unsorted(spkadd_plan_s* p, hipStream_t s) {
   }
   p->release(d_q, s);
   p->n_windows = W;
-  p->max_span = p->h_sum->max_span;
   // buckets: offsets, boundaries in the one-input layout, then the partition
   int* d_boff = nullptr;
   int* d_gcur = nullptr;
@@ -813,35 +817,18 @@ bool layout_bin(const spkadd_plan_s* p, int b, bool numeric, KArgs& a, int& acc)
   return false;
 }
 
-// Workgroup units (G1, G2, windows) narrow enough for a bitmap over their row range
-// use it, unless hash tables are asked for (accum_mode, or the degenerate-hash test
-// hook, which is about the tables).
+// Workgroup units take the workgroup bitmap, unless hash tables are asked for
+// (accum_mode, or the degenerate-hash test hook, which is about the tables).
+bool wg_bitmap(const spkadd_opts& o) { return o.accum_mode != SPKADD_ACCUM_HASH && o.hash_mode == 0; }
+
 bool wg_bitmap_bin(const spkadd_plan_s* p, int b) {
-  if (b != BIN_G1 && b != BIN_G2 && b != BIN_WIN) return false;
-  if (p->opts.accum_mode == SPKADD_ACCUM_HASH || p->opts.hash_mode != 0) return false;
-  return b == BIN_WIN || p->m <= bitmap_wg_span_max();
+  return (b == BIN_G1 || b == BIN_G2 || b == BIN_G3 || b == BIN_WIN) && wg_bitmap(p->opts);
 }
 
-// The bitmap is sized for the widest unit of the bin (rounded up to a power of two,
-// at most bitmap_wg_span_max()); worst: the largest it can be (before the windows exist).
-void wg_bitmap_layout(const spkadd_plan_s* p, int b, bool numeric, KArgs& a, bool worst = false) {
-  const int cap = bitmap_wg_span_max();
-  const long long need = worst ? cap : b == BIN_WIN ? p->max_span : p->m;
-  int span = 1024;
-  while (span < need && span < cap) span <<= 1;
-  const int vb = p->dtype == SPKADD_F64 ? 8 : 4, regs = bitmap_wg_regs(b);
-  lds_layout_bitmap_wg(numeric, vb, p->k, span, p->pp.cap_in, regs, false, 2, a);
-  if (!numeric) return;
-  // groups of four words halve the prefix; worth their costlier ranks only where that
-  // lets another workgroup reside (resident waves per CU are capped at 32)
-  KArgs a4 = a;
-  lds_layout_bitmap_wg(numeric, vb, p->k, span, p->pp.cap_in, regs, false, 4, a4);
-  const int waves = (b == BIN_G1 ? G1_THREADS : G2_THREADS) / 64, lmax = max_lds_bytes();
-  auto resident = [&](const KArgs& x) {
-    const int by_lds = lmax / (x.slice_bytes > 0 ? x.slice_bytes : 1), by_waves = 32 / waves;
-    return by_lds < by_waves ? by_lds : by_waves;
-  };
-  if (resident(a4) > resident(a)) a = a4;
+void wg_bitmap_layout(const spkadd_plan_s* p, int b, bool numeric, KArgs& a) {
+  const int cap = b == BIN_G1 ? p->pp.g1_max : b == BIN_G3 ? p->pp.g3_max : p->pp.cap_in;
+  lds_layout_bitmap_wg(numeric, p->dtype == SPKADD_F64 ? 8 : 4, p->k, cap, bitmap_wg_threads(b, cap) * BITMAP_WG_EW,
+                       p->m, a);
 }
 
 // Launches the symbolic or numeric kernel of bin b.
@@ -859,17 +846,8 @@ hipError_t launch_bin(spkadd_plan_s* p, int b, bool numeric, KArgs& a_in, hipStr
   const bool f64 = p->dtype == SPKADD_F64;
   const int* list = b == BIN_WIN ? nullptr : p->d_list + p->binoff[b];
   if (wg_bitmap_bin(p, b)) {
-    // workgroup bitmap for every unit at most span_max rows wide; the hash kernel
-    // takes the wider ones (only windows can be wider)
-    KArgs ab = a;
-    wg_bitmap_layout(p, b, numeric, ab);
-    hipError_t e = launch_bitmap_wg(b, numeric, f64, ab, list, cnt, s);
-    if (e != hipSuccess || b != BIN_WIN || p->max_span <= ab.wg_span_max) return e;
-    int acc = 0;
-    layout_bin(p, b, numeric, a, acc);
-    a.wg_span_max = ab.wg_span_max;
-    TraceScope t(p, numeric ? "num_window_wide" : "sym_window_wide", s, numeric);
-    return launch_hash(b, numeric, f64, a, list, cnt, s);
+    wg_bitmap_layout(p, b, numeric, a);
+    return launch_bitmap_wg(b, numeric, f64, a, list, cnt, s);
   }
   int acc = 0;
   if (layout_bin(p, b, numeric, a, acc)) return launch_wave_pipe(b, numeric, f64, acc, a, list, cnt, p->n_cu, s);
@@ -962,7 +940,9 @@ spkadd_status plan_build(spkadd_plan_s* p, int32_t m, int32_t n, int32_t k, cons
   p->dtype = dtype;
   p->opts = o;
   p->last_stream = stream;
-  const int cap = o.window_cap ? o.window_cap : (dtype == SPKADD_F64 ? kDefaultCapF64 : kDefaultCapF32);
+  const bool f64 = dtype == SPKADD_F64, small_cap = !wg_bitmap(o) || (o.flags & SPKADD_FLAG_ORDERED) || n < kManyCols;
+  const int hash_cap = o.window_cap ? o.window_cap : f64 ? kHashCapF64 : kHashCapF32;
+  const int cap = o.window_cap || small_cap ? hash_cap : f64 ? kDefaultCapF64 : kDefaultCapF32;
   const float asym = o.load_factor_sym > 0 ? o.load_factor_sym : kDefaultAlphaSym;
   const float anum = o.load_factor_num > 0 ? o.load_factor_num : kDefaultAlphaNum;
   p->alpha_sym_q = alpha_to_q(asym);
@@ -977,26 +957,19 @@ spkadd_status plan_build(spkadd_plan_s* p, int32_t m, int32_t n, int32_t k, cons
   int g1 = cap < 2048 ? cap : 2048;
   while (g1 > 64 && table_slots(g1, p->alpha_num_q) > G1_THREADS * 16) g1 -= 64;
   p->pp.g1_max = g1;
+  p->pp.g3_max = o.window_cap || small_cap ? cap : f64 ? kG3MaxF64 : kG3MaxF32;
   p->pp.force_bin = o.force_bin;
   p->pp.win_fill = o.window_fill > 0 ? o.window_fill : kDefaultFill;
   p->unsorted_in = (o.flags & SPKADD_FLAG_UNSORTED_IN) != 0;
   p->pp.unsorted_in = p->unsorted_in ? 1 : 0;
-  // windows no wider than the workgroup bitmap, so that none falls back to hash
-  // tables (unless hash tables are asked for)
-  p->pp.win_min = 1;
-  p->pp.win_span = INT_MAX;
-  if (o.accum_mode != SPKADD_ACCUM_HASH && o.hash_mode == 0 && m > bitmap_wg_span_max()) {
-    p->pp.win_min = (int)(((long long)m + bitmap_wg_span_max() - 1) / bitmap_wg_span_max());
-    p->pp.win_span = bitmap_wg_span_max();
-  }
   for (int b = BIN_W1; b <= BIN_W16; ++b) {
     p->ts_sym[b] = table_slots(64 * wave_bin_E(b), p->alpha_sym_q);
     p->ts_num[b] = table_slots(64 * wave_bin_E(b), p->alpha_num_q);
   }
   p->ts_sym[BIN_G1] = table_slots(p->pp.g1_max, p->alpha_sym_q);
   p->ts_num[BIN_G1] = table_slots(p->pp.g1_max, p->alpha_num_q);
-  p->ts_sym[BIN_G2] = p->ts_sym[BIN_WIN] = table_slots(cap, p->alpha_sym_q);
-  p->ts_num[BIN_G2] = p->ts_num[BIN_WIN] = table_slots(cap, p->alpha_num_q);
+  p->ts_sym[BIN_G2] = p->ts_sym[BIN_WIN] = table_slots(hash_cap, p->alpha_sym_q);
+  p->ts_num[BIN_G2] = p->ts_num[BIN_WIN] = table_slots(hash_cap, p->alpha_num_q);
   if (p->ts_num[BIN_G1] > G1_THREADS * 16 || p->ts_num[BIN_G2] > G2_THREADS * 32)
     return fail(set_error(SPKADD_ERR_INVALID, "window_cap / load_factor_num give too large numeric tables"));
   if (o.flags & SPKADD_FLAG_ORDERED) {
@@ -1347,7 +1320,7 @@ spkadd_status spkadd_get_stats(spkadd_plan_t p, spkadd_stats* out) {
   s.nnz_out = p->sym_done ? p->nnz_c : -1;
   s.n_empty_cols = p->bin_count[BIN_EMPTY];
   for (int b = BIN_W1; b <= BIN_W16; ++b) s.n_wave_cols += p->bin_count[b];
-  s.n_wg_cols = p->bin_count[BIN_G1] + p->bin_count[BIN_G2];
+  s.n_wg_cols = p->bin_count[BIN_G1] + p->bin_count[BIN_G2] + p->bin_count[BIN_G3];
   s.n_window_cols = p->n_wcols;
   s.n_windows = p->n_windows;
   s.window_levels = p->levels;

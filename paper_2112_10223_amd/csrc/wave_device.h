@@ -65,7 +65,10 @@ template <int E, bool NUM, typename V>
 __device__ __forceinline__ void issue_unit_loads(const KArgs& a, unsigned char* base, const long long* adj, int u,
                                                  int (&rows)[E], V (&vals)[E]) {
   const int lane = lane_id();
-  const unsigned long long* sb = reinterpret_cast<const unsigned long long*>(base + a.off_mark);
+  // lane t holds the start mask's word t
+  const unsigned long long sw =
+      reinterpret_cast<const unsigned long long*>(base + a.off_mark)[E == 16 ? lane & 15 : min(lane, E - 1)];
+  const int swl = (int)(unsigned)sw, swh = (int)(unsigned)(sw >> 32);
   int before = -1;  // starts in earlier chunks, minus one
   // (addresses of a few entries at a time: more of them would only cost registers)
   constexpr int CH = lookup_group(E);
@@ -75,10 +78,8 @@ __device__ __forceinline__ void issue_unit_loads(const KArgs& a, unsigned char* 
   long long ar[CH], av[CH];
 #pragma unroll
   for (int t = 0; t < CH; ++t) {
-    const unsigned long long w = sb[t0 + t];
-    // (the builtin returns int: go through unsigned so the low word is not sign-extended)
-    const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(w >> 32));
-    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)w);
+    // (readlane returns int: go through unsigned so the low word is not sign-extended)
+    const unsigned hi = (unsigned)readlane(swh, t0 + t), lo = (unsigned)readlane(swl, t0 + t);
     const unsigned long long S = ((unsigned long long)hi << 32) | (unsigned long long)lo;
     const int seg = before + (int)(S & 1ull) + mbcnt(S >> 1);
     before += __popcll(S);
@@ -425,13 +426,23 @@ __device__ __forceinline__ void bitmap_ranks(const unsigned* bm, const unsigned 
   }
 }
 
+// ORs bit r into the bitmap; returns its word before, masked to the bit.  A lane past
+// the end (in false) ORs nothing, into a word of its own: 64 lanes at the copies' one
+// word would take the LDS 64 turns (row windows with such groups skipped: R-MAT scale
+// 20, 64 inputs, symbolic 2314 -> 1195 us).
+__device__ __forceinline__ unsigned or_bit(unsigned* bm, int r, bool in) {
+  const unsigned bit = in ? 1u << (r & 31) : 0u;
+  return atomicOr(&bm[in ? r >> 5 : lane_id()], bit) & bit;
+}
+
 // Ranked bitmap: the rows of a unit (lanes past the end hold a copy of its last row)
 // as bit numbers below 4096 E in the rows' order.  The top level marks the non-empty
 // blocks of 2^rk_shift rows; a block's rank replaces its number, which leaves at most
 // 64 E blocks.  While blocks are larger than 64 rows, they are divided into 64 again
 // and ranked again.  A row outside the matrix (invalid input) counts as its last.
 template <int E>
-__device__ __forceinline__ void rank_rows(const KArgs& a, unsigned char* base, const int (&rows)[E], int (&vr)[E]) {
+__device__ __forceinline__ void rank_rows(const KArgs& a, unsigned char* base, int u, const int (&rows)[E],
+                                          int (&vr)[E]) {
   const int lane = lane_id();
   uint4* bm4 = reinterpret_cast<uint4*>(base);
   unsigned* bm = reinterpret_cast<unsigned*>(base);
@@ -445,8 +456,7 @@ __device__ __forceinline__ void rank_rows(const KArgs& a, unsigned char* base, c
     wave_sync();
 #pragma unroll
     for (int t = 0; t < E; ++t) {
-      const int blk = vr[t] >> sh;
-      atomicOr(&bm[blk >> 5], 1u << (blk & 31));
+      (void)or_bit(bm, vr[t] >> sh, lane + 64 * t < u);
     }
     wave_sync();
     bitmap_prefix(bm4, reinterpret_cast<unsigned*>(pw), nq);
@@ -458,42 +468,44 @@ __device__ __forceinline__ void rank_rows(const KArgs& a, unsigned char* base, c
 }
 
 // ORs the rows' bits (vr) into the bitmap; returns the bits this lane found clear.
-// Lanes past the end hold a copy of the unit's last row: its bit is found clear once,
-// by whichever lane comes first, so they need no mask.
 template <int E>
-__device__ __forceinline__ int count_new(unsigned* bm, const int (&vr)[E]) {
-  int seen = 0;
+__device__ __forceinline__ int count_new(unsigned* bm, int u, const int (&vr)[E]) {
+  const int lane = lane_id();
+  int newc = 0;
 #pragma unroll
-  for (int t = 0; t < E; ++t)
-    seen += (int)__builtin_amdgcn_ubfe(atomicOr(&bm[vr[t] >> 5], 1u << (vr[t] & 31)), (unsigned)(vr[t] & 31), 1u);
-  return E - seen;
+  for (int t = 0; t < E; ++t) {
+    const bool in = lane + 64 * t < u;
+    newc += (or_bit(bm, vr[t], in) == 0u && in) ? 1 : 0;
+  }
+  return newc;
 }
 
 // Symbolic: OR the rows in; an OR that finds its bit clear counts a new row.  The
 // bitmap is all zero on entry (cleared at the start of the run) and is left all
 // zero: the words the unit touched are cleared again.
 template <int E>
-__device__ __forceinline__ int bm_sym_unit(const KArgs& a, unsigned char* base, const int (&rows)[E]) {
+__device__ __forceinline__ int bm_sym_unit(const KArgs& a, unsigned char* base, int u, const int (&rows)[E]) {
+  const int lane = lane_id();
   unsigned* bm = reinterpret_cast<unsigned*>(base + a.off_bm);
-  const int newc = count_new<E>(bm, rows);
+  const int newc = count_new<E>(bm, u, rows);
   wave_sync();
 #pragma unroll
-  for (int t = 0; t < E; ++t) bm[rows[t] >> 5] = 0u;
+  for (int t = 0; t < E; ++t) bm[lane + 64 * t < u ? rows[t] >> 5 : lane] = 0u;
   wave_sync();
   return wave_total_add(newc);
 }
 
 // Symbolic over the ranked bitmap (cleared for every unit).
 template <int E>
-__device__ __forceinline__ int rk_sym_unit(const KArgs& a, unsigned char* base, const int (&rows)[E]) {
+__device__ __forceinline__ int rk_sym_unit(const KArgs& a, unsigned char* base, int u, const int (&rows)[E]) {
   const int lane = lane_id();
   uint4* bm4 = reinterpret_cast<uint4*>(base);
   int vr[E];
-  rank_rows<E>(a, base, rows, vr);
+  rank_rows<E>(a, base, u, rows, vr);
 #pragma unroll
   for (int q = 0; q < rk_low_rows(E); ++q) bm4[q * 64 + lane] = make_uint4(0u, 0u, 0u, 0u);
   wave_sync();
-  const int newc = count_new<E>(reinterpret_cast<unsigned*>(base), vr);
+  const int newc = count_new<E>(reinterpret_cast<unsigned*>(base), u, vr);
   wave_sync();
   return wave_total_add(newc);
 }
@@ -513,7 +525,7 @@ __device__ __forceinline__ void bm_num_unit(const KArgs& a, unsigned char* base,
   const int nq = RK ? rk_low_rows(E) : a.bm_nq;
   int vr[E];  // the bits of the rows
   if constexpr (RK) {
-    rank_rows<E>(a, base, rows, vr);
+    rank_rows<E>(a, base, u, rows, vr);
   } else {
 #pragma unroll
     for (int t = 0; t < E; ++t) vr[t] = rows[t];
@@ -523,11 +535,8 @@ __device__ __forceinline__ void bm_num_unit(const KArgs& a, unsigned char* base,
   bool first[E];
 #pragma unroll
   for (int t = 0; t < E; ++t) {
-    // lanes past the end hold a copy of the unit's last row and OR nothing
     const bool in = lane + 64 * t < u;
-    const unsigned bit = in ? 1u << (vr[t] & 31) : 0u;
-    const unsigned old = atomicOr(&bm[vr[t] >> 5], bit);
-    first[t] = in && (old & bit) == 0;
+    first[t] = or_bit(bm, vr[t], in) == 0u && in;
   }
   wave_sync();
   int c = bitmap_prefix(bm4, reinterpret_cast<unsigned*>(pw), nq);
@@ -643,7 +652,8 @@ __device__ __forceinline__ void pipe_step(const KArgs& a, unsigned char* base, i
   } else if constexpr (NUM) {
     num_unit<E, V>(a, base, cur.u, cur.cnt, cur.o0, cur.j >= 0, cur.rows, cur.vals);
   } else if constexpr (ACC != ACC_HASH) {
-    const int cnt = ACC == ACC_RANKED ? rk_sym_unit<E>(a, base, cur.rows) : bm_sym_unit<E>(a, base, cur.rows);
+    const int cnt = ACC == ACC_RANKED ? rk_sym_unit<E>(a, base, cur.u, cur.rows)
+                                      : bm_sym_unit<E>(a, base, cur.u, cur.rows);
     // one unconditional store instruction: lane 0 writes the count, the other
     // lanes (and replayed units) write into their write-sink slots
     const long long dmy = (long long)a.dummy + 2048 + 8LL * lane;

@@ -105,3 +105,33 @@ def test_batched_requests_with_few_entries():
                    q["values_c"][:z].cpu().numpy())
             assert_matches(b, got, oracle.spkadd(b), exact_values=True)
         bt.close()
+
+
+WG_SIZES = [1025, 1500, 2047, 2048, 2049, 3072, 3073, 4095, 4096, 4097, 5000, 6143, 6144, 6145, 8191, 8192, 8193, 12000,
+            30000, 0, 3]
+
+
+@pytest.mark.parametrize("m", [9000, 131072, 131073, 1 << 20, 40960 * 32 + 1, 163840 * 32 + 1, 1 << 27, (1 << 31) - 2])
+@pytest.mark.parametrize("k", [1, 6, 64, 130])
+def test_workgroup_levels(m, k):
+    """Workgroup columns of all three sizes and row windows: one bit per row, one and two
+    levels of ranked blocks; 64 columns and more take the large capacities."""
+    dtype = np.float64 if (m // 7 + k) % 2 else np.float32
+    integers = k in (6, 64)
+    note(f"workgroup bitmap levels m={m} k={k} {dtype.__name__} integers={integers}")
+    b = tall_batch(m, k, (WG_SIZES * 4)[:70], dtype, integers, seed=m % 1000 + k)
+    got = run_gpu(b, _opts(), stats=True)
+    assert got[3]["n_wg_cols"] > 0 and (m < 10000 or got[3]["n_window_cols"] > 0)
+    assert_matches(b, got, oracle.spkadd(b), exact_values=integers)
+
+
+@pytest.mark.parametrize("window_cap", [64, 1000, 4096, 5000, 8192])
+def test_window_capacities(window_cap):
+    """Windows in 512 and 1024 threads, windows of more entries than registers (dense rows),
+    every column forced to windows."""
+    for m, k, sizes in ((3000, 20, [40000, 9000, 100, 2500]), (1 << 21, 9, [40000, 9000, 100, 2500])):
+        note(f"window_cap={window_cap} m={m}")
+        b = tall_batch(m, k, sizes * 2, np.float32, True, seed=window_cap + k)
+        ref = oracle.spkadd(b)
+        for force in (-1, 1, 2):
+            assert_matches(b, run_gpu(b, _opts(window_cap=window_cap, force_bin=force)), ref, exact_values=True)
