@@ -56,14 +56,6 @@ __device__ __forceinline__ void in_fours(int t) {
   if (t > 0 && t % 4 == 0) __builtin_amdgcn_sched_barrier(0);
 }
 
-// Between the passes over a unit's entries: keeps the compiler from carrying word
-// addresses, bits and masks of every entry over a barrier instead of forming them again.
-template <int EW>
-__device__ __forceinline__ void forget_derived(int (&vr)[EW]) {
-#pragma unroll
-  for (int t = 0; t < EW; ++t) asm volatile("" : "+v"(vr[t]));
-}
-
 // Set bits below bit r.
 __device__ __forceinline__ int bitmap_rank(const unsigned* bm, const unsigned short* pw, int r) {
   const uint2 pr = reinterpret_cast<const uint2*>(bm)[r >> 6];

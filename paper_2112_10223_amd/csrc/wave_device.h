@@ -50,10 +50,12 @@ __host__ __device__ inline void rk_levels(int m, int& shift, int& nq) {
 __host__ __device__ constexpr int sym_meta_rows(int KC) { return KC; }
 
 // Entries of a lane whose table lookups are in flight together.  Up to E = 10 all of
-// them; above, the registers they hold cost resident wavefronts (numeric bitmap, fp32,
-// E = 12 / 16: 141 / 179 registers in one group, three / two wavefronts per SIMD; 127 /
-// 161 in these groups, four / three).
-__host__ __device__ constexpr int lookup_group(int E) { return E <= 10 ? E : E == 12 ? 6 : 4; }
+// them; above, the registers they hold cost resident wavefronts.  With the ranked
+// bitmap that starts at E = 10 (129 registers and three wavefronts per SIMD, 126 and four
+// in groups of five: 96 -> 76 us on 32,768 columns of 480 entries).
+__host__ __device__ constexpr int lookup_group(int E, bool ranked) {
+  return E <= 8 ? E : E == 10 ? (ranked ? 5 : 10) : 4;
+}
 
 // Entry addresses of one unit.  The non-empty segments (inputs with entries in the
 // column) are numbered in order, and each sets the bit of its start position in a
@@ -61,7 +63,7 @@ __host__ __device__ constexpr int lookup_group(int E) { return E <= 10 ? E : E =
 // - 1: per chunk of 64 positions, the starts of earlier chunks (a scalar count)
 // plus mbcnt over the chunk's mask word.  Lanes past the end take the unit's last
 // entry (every unit has u > 0), so no load is masked off.
-template <int E, bool NUM, typename V>
+template <int E, bool NUM, typename V, int ACC>
 __device__ __forceinline__ void issue_unit_loads(const KArgs& a, unsigned char* base, const long long* adj, int u,
                                                  int (&rows)[E], V (&vals)[E]) {
   const int lane = lane_id();
@@ -71,7 +73,7 @@ __device__ __forceinline__ void issue_unit_loads(const KArgs& a, unsigned char* 
   const int swl = (int)(unsigned)sw, swh = (int)(unsigned)(sw >> 32);
   int before = -1;  // starts in earlier chunks, minus one
   // (addresses of a few entries at a time: more of them would only cost registers)
-  constexpr int CH = lookup_group(E);
+  constexpr int CH = lookup_group(E, ACC == ACC_RANKED);
 #pragma unroll
   for (int t0 = 0; t0 < E; t0 += CH) {
   if (t0 > 0) __builtin_amdgcn_sched_barrier(0);
@@ -155,8 +157,8 @@ __device__ __forceinline__ int build_unit_meta(const KArgs& a, unsigned char* ba
 
 // Coalesced write-out of an output column staged in LDS (rows br[0..c), values
 // bv[0..c), rows ascending) at offset o0 of rowidx(B) / values(B).  Lanes past the
-// end repeat the last entry's store (same address, same value).  With c == 0 (a
-// replayed or failed unit) every lane stores into the write sink instead.  The base
+// end repeat the last entry's store (same address, same value).  With c == 0 (a failed
+// unit) every lane stores into the write sink instead.  The base
 // pointers are the same for the whole wavefront, so only the offsets are per lane.
 template <int E, typename V>
 __device__ __forceinline__ void write_column(const KArgs& a, int o0, int c, const int* br, const V* bv) {
@@ -245,8 +247,8 @@ __device__ __forceinline__ int insert_batch(int* K, V* Vt, int TS, int mode, int
 // write-out.  The key and value arrays have 64 extra sink slots after ts_max; lanes
 // without an entry write there, so no store is predicated.
 template <int E, typename V>
-__device__ __forceinline__ void num_unit(const KArgs& a, unsigned char* base, int u, int cnt, int o0, bool live,
-                                         const int (&rows)[E], const V (&vals)[E]) {
+__device__ __forceinline__ void num_unit(const KArgs& a, unsigned char* base, int u, int cnt, int o0, const int (&rows)[E],
+                                         const V (&vals)[E]) {
   constexpr int NCH = 2 * E;  // 64-slot table chunks at load factor 1/2
   constexpr int RANK_UNROLL = 4;
   const int lane = lane_id();
@@ -286,7 +288,6 @@ __device__ __forceinline__ void num_unit(const KArgs& a, unsigned char* base, in
     if (lane == 0) atomicOr(a.err, ERR_COUNT);
     nc = 0;  // write nothing for this unit
   }
-  if (!live) nc = 0;  // a replayed unit writes nothing
   if (a.unsorted) {  // (uniform) table order
     wave_sync();
     write_column<E, V>(a, o0, nc, K, Vt);
@@ -399,10 +400,10 @@ __device__ __forceinline__ int bitmap_prefix(const uint4* bm4, unsigned* pw32, i
 // into an indexed scratch access.)
 // BLOCKS: the bits are those of the blocks r >> sh, and rk gets the block's rank in
 // place of its number (r and rk may be the same array).
-template <int E, bool BLOCKS = false>
+template <int E, bool RANKED, bool BLOCKS = false>
 __device__ __forceinline__ void bitmap_ranks(const unsigned* bm, const unsigned short* pw, const int (&r)[E],
                                              int (&rk)[E], int sh = 0) {
-  constexpr int CH = lookup_group(E);
+  constexpr int CH = lookup_group(E, RANKED);
 #pragma unroll
   for (int t0 = 0; t0 < E; t0 += CH) {
     if (t0 > 0) __builtin_amdgcn_sched_barrier(0);
@@ -424,6 +425,15 @@ __device__ __forceinline__ void bitmap_ranks(const unsigned* bm, const unsigned 
       rk[t0 + t] = BLOCKS ? (below << sh) | (r[t0 + t] & ((1 << sh) - 1)) : below;
     }
   }
+}
+
+// Between the passes over a unit's entries: keeps the compiler from carrying word
+// addresses, bits and masks of every entry from one pass to the next instead of forming
+// them again (registers, and with them resident wavefronts).
+template <int EW>
+__device__ __forceinline__ void forget_derived(int (&vr)[EW]) {
+#pragma unroll
+  for (int t = 0; t < EW; ++t) asm volatile("" : "+v"(vr[t]));
 }
 
 // ORs bit r into the bitmap; returns its word before, masked to the bit.  A lane past
@@ -459,9 +469,11 @@ __device__ __forceinline__ void rank_rows(const KArgs& a, unsigned char* base, i
       (void)or_bit(bm, vr[t] >> sh, lane + 64 * t < u);
     }
     wave_sync();
+    forget_derived<E>(vr);
     bitmap_prefix(bm4, reinterpret_cast<unsigned*>(pw), nq);
     wave_sync();
-    bitmap_ranks<E, true>(bm, pw, vr, vr, sh);
+    bitmap_ranks<E, true, true>(bm, pw, vr, vr, sh);
+    forget_derived<E>(vr);
     wave_sync();
     nq = rk_low_rows(E);
   }
@@ -512,7 +524,7 @@ __device__ __forceinline__ int rk_sym_unit(const KArgs& a, unsigned char* base, 
 
 // RK: over the ranked bitmap, whose levels all start at the slice's base.
 template <int E, typename V, bool RK>
-__device__ __forceinline__ void bm_num_unit(const KArgs& a, unsigned char* base, int u, int cnt, int o0, bool live,
+__device__ __forceinline__ void bm_num_unit(const KArgs& a, unsigned char* base, int u, int cnt, int o0,
                                             const int (&rows)[E], const V (&vals)[E]) {
   const int lane = lane_id();
   uint4* bm4 = reinterpret_cast<uint4*>(base + a.off_bm);
@@ -539,17 +551,18 @@ __device__ __forceinline__ void bm_num_unit(const KArgs& a, unsigned char* base,
     first[t] = or_bit(bm, vr[t], in) == 0u && in;
   }
   wave_sync();
+  if constexpr (RK) forget_derived<E>(vr);  // (the other bitmap is faster without, at the same residency)
   int c = bitmap_prefix(bm4, reinterpret_cast<unsigned*>(pw), nq);
   if (c != cnt) {
     if (lane == 0) atomicOr(a.err, ERR_COUNT);
     c = 0;
   }
-  if (!live) c = 0;  // a replayed unit writes nothing
   wave_sync();
   // rank(row) = set bits below it = output position; the first entry of a row puts
   // the row and its value there, later entries of the row add their values
   int rk[E];
-  bitmap_ranks<E>(bm, pw, vr, rk);
+  bitmap_ranks<E, RK>(bm, pw, vr, rk);
+  if constexpr (RK) forget_derived<E>(rk);
   wave_sync();  // the bitmap is read for the last time above
   // entries that are not first write into per-lane sink slots 64 E + lane
 #pragma unroll
@@ -622,9 +635,11 @@ struct UnitRegs {
 
 // One pipeline step: finish the metadata of unit t+1, start loads for units t+2
 // (pointers) and t+1 (entries), then process unit t.
-// Steps t >= nu (the loop runs an even count) replay the wavefront's last unit with
-// its output sent to the write sink: every step runs the same instruction sequence
-// on a real column, so the compiler keeps the next unit's loads in flight.
+// Every step runs the same instruction sequence, so the compiler keeps the next unit's
+// loads in flight (after the last unit the loads are of that unit again, unused).  The
+// loop leaves after either step: replaying the last unit into the write sink to fill up
+// an even count had every wavefront of the chip store to one cache line (16 inputs of
+// 1,000,003 x 150,001: odd counts 258 us, even ones 162).
 template <int E, bool NUM, typename V, int ACC, int KC>
 __device__ __forceinline__ void pipe_step(const KArgs& a, unsigned char* base, int t, int nu, int ucol,
                                           const long long (&cpp)[KC], const long long (&rip)[KC],
@@ -636,7 +651,7 @@ __device__ __forceinline__ void pipe_step(const KArgs& a, unsigned char* base, i
     // one segment table: a unit's pointers are read into registers in the step
     // that writes them
     long long* adj = (long long*)(base + a.off_adj);
-    nxt.j = t + 1 < nu ? readlane(ucol, t + 1) : -1;  // -1: a replay, no output
+    nxt.j = readlane(ucol, min(t + 1, nu - 1));
     nxt.u = build_unit_meta<E, NUM, V, KC>(a, base, rip, vap, ms, me, adj);
     if (NUM) {
       nxt.o0 = readlane(mc, 0);
@@ -644,20 +659,19 @@ __device__ __forceinline__ void pipe_step(const KArgs& a, unsigned char* base, i
     }
     issue_meta_loads<NUM, KC>(a, cpp, readlane(ucol, min(t + 2, nu - 1)), ms, me, mc);
     wave_sync();
-    issue_unit_loads<E, NUM, V>(a, base, adj, nxt.u, nxt.rows, nxt.vals);
+    issue_unit_loads<E, NUM, V, ACC>(a, base, adj, nxt.u, nxt.rows, nxt.vals);
     if constexpr (!NUM && ACC == ACC_BITMAP) clear_meta<KC>(a, base);
   }
   if constexpr (NUM && ACC != ACC_HASH) {
-    bm_num_unit<E, V, ACC == ACC_RANKED>(a, base, cur.u, cur.cnt, cur.o0, cur.j >= 0, cur.rows, cur.vals);
+    bm_num_unit<E, V, ACC == ACC_RANKED>(a, base, cur.u, cur.cnt, cur.o0, cur.rows, cur.vals);
   } else if constexpr (NUM) {
-    num_unit<E, V>(a, base, cur.u, cur.cnt, cur.o0, cur.j >= 0, cur.rows, cur.vals);
+    num_unit<E, V>(a, base, cur.u, cur.cnt, cur.o0, cur.rows, cur.vals);
   } else if constexpr (ACC != ACC_HASH) {
     const int cnt = ACC == ACC_RANKED ? rk_sym_unit<E>(a, base, cur.u, cur.rows)
                                       : bm_sym_unit<E>(a, base, cur.u, cur.rows);
-    // one unconditional store instruction: lane 0 writes the count, the other
-    // lanes (and replayed units) write into their write-sink slots
-    const long long dmy = (long long)a.dummy + 2048 + 8LL * lane;
-    gstore<int>(lane == 0 && cur.j >= 0 ? (long long)(a.colcnt + cur.j) : dmy, cnt);
+    // one unconditional store instruction: every lane writes the count to its place (one
+    // request; write-sink slots for the other lanes would be lines shared by the whole chip)
+    gstore<int>((long long)(a.colcnt + cur.j), cnt);
     wave_sync();
   } else {
     int* T = (int*)base;
@@ -667,8 +681,7 @@ __device__ __forceinline__ void pipe_step(const KArgs& a, unsigned char* base, i
     wave_sync();
     const int newc = insert_batch<E, false, V>(T, nullptr, TS, a.hash_mode, cur.u, cur.rows, cur.vals, a.err);
     const int cnt = wave_total_add(newc);
-    const long long dmy = (long long)a.dummy + 2048 + 8LL * lane;
-    gstore<int>(lane == 0 && cur.j >= 0 ? (long long)(a.colcnt + cur.j) : dmy, cnt);
+    gstore<int>((long long)(a.colcnt + cur.j), cnt);
     wave_sync();
   }
 }
@@ -701,7 +714,7 @@ __device__ __forceinline__ void run_pipe(const KArgs& a, unsigned char* base, in
     }
     issue_meta_loads<NUM, KC>(a, cpp, readlane(ucol, min(1, nu - 1)), ms, me, mc);
     wave_sync();
-    issue_unit_loads<E, NUM, V>(a, base, adj, A.u, A.rows, A.vals);
+    issue_unit_loads<E, NUM, V, ACC>(a, base, adj, A.u, A.rows, A.vals);
   }
   if constexpr (!NUM && ACC == ACC_BITMAP) {  // the symbolic bitmap starts all zero and stays so
     wave_sync();
@@ -710,10 +723,11 @@ __device__ __forceinline__ void run_pipe(const KArgs& a, unsigned char* base, in
     wave_sync();
   }
   prime_stores<E, NUM, V>(a);
-  const int steps = (nu + 1) & ~1;
-  for (int t = 0; t < steps; t += 2) {
+  for (int t = 0;;) {
     pipe_step<E, NUM, V, ACC, KC>(a, base, t, nu, ucol, cpp, rip, vap, ms, me, mc, A, B);
-    pipe_step<E, NUM, V, ACC, KC>(a, base, t + 1, nu, ucol, cpp, rip, vap, ms, me, mc, B, A);
+    if (++t >= nu) break;  // (uniform)
+    pipe_step<E, NUM, V, ACC, KC>(a, base, t, nu, ucol, cpp, rip, vap, ms, me, mc, B, A);
+    if (++t >= nu) break;
   }
 }
 
