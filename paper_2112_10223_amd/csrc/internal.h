@@ -75,9 +75,13 @@ struct PlanSummary {
   int pad;       // windows still to refine (one refinement level)
 };
 
+// Ints per column of the column-by-column copy of the column pointers (16-byte rows).
+__host__ __device__ inline int cpt_stride(int k) { return (k + 3) & ~3; }
+
 // Arguments of the per-unit symbolic / numeric kernels.
 struct KArgs {
   const int* const* cp;   // k device colptr pointers
+  const int* cpt;         // the colptr arrays column by column (colptr_i[j] at j * cpt_stride(k) + i), or nullptr
   const int* const* ri;   // k device rowidx pointers
   const void* const* va;  // k device value pointers (numeric)
   int m, n, k;

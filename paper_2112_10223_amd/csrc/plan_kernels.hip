@@ -25,11 +25,27 @@ __device__ __forceinline__ int classify(long long u, const PlanParams& p) {
   return u <= p.g3_max ? BIN_G3 : BIN_WIN;
 }
 
-// u_j = sum_i nnz(A_i(:,j)), bin of j, per-block bin histogram, nnz_in.
+// The column pointers of 16 inputs (i0 ..) at column j into the column-by-column copy
+// (a row's last places past input k - 1 hold copies, unused).
+__device__ __forceinline__ void put_colptrs(int* __restrict__ cpt, int k, long long j, int i0, const int (&v)[16]) {
+  const int ks = cpt_stride(k);
+  int4* o = reinterpret_cast<int4*>(cpt + j * ks + i0);
+#pragma unroll
+  for (int t = 0; t < 16; t += 4)
+    if (i0 + t < ks) o[t >> 2] = make_int4(v[t], v[t + 1], v[t + 2], v[t + 3]);
+}
+
+// u_j = sum_i nnz(A_i(:,j)), bin of j, per-block bin histogram, nnz_in.  cpt (when not
+// null) receives the colptr arrays column by column: the symbolic and numeric kernels
+// read a column's 2 k pointers there from two short runs of memory, instead of from k
+// arrays (k cache lines and k pages a column; with 64 inputs half of such reads missed
+// the address translation cache).  R-MAT scale 20, 64 inputs: this kernel 74 -> 228 us,
+// symbolic wave bins 1117 -> 484, numeric E = 1 774 -> 287; 128 inputs of 65,536 x 16,384:
+// symbolic 152 -> 67, numeric 177 -> 120.
 __global__ __launch_bounds__(PLAN_THREADS) void k_bounds(PlanParams p, const int* const* __restrict__ cp,
                                                          const int* const* __restrict__ ri, int* __restrict__ u, unsigned char* __restrict__ bin,
                                                          int* __restrict__ colcnt, int* __restrict__ hist,
-                                                         PlanSummary* __restrict__ sum) {
+                                                         int* __restrict__ cpt, PlanSummary* __restrict__ sum) {
   __shared__ int wh[PLAN_THREADS / 64][NBINS];
   __shared__ unsigned long long red[PLAN_THREADS / 64 + 1];
   if (blockIdx.x == 0)  // an input with entries must come with a row array
@@ -53,6 +69,10 @@ __global__ __launch_bounds__(PLAN_THREADS) void k_bounds(PlanParams p, const int
       for (int t = 0; t < 16; ++t) {
         s[t] = gload<int>(ptr[t] + 4LL * j);
         e[t] = gload<int>(ptr[t] + 4LL * (j + 1));
+      }
+      if (cpt) {
+        put_colptrs(cpt, p.k, j, i0, s);
+        if (j == p.n - 1) put_colptrs(cpt, p.k, p.n, i0, e);
       }
 #pragma unroll
       for (int t = 0; t < 16; ++t)
@@ -953,9 +973,9 @@ static inline unsigned grid_for(long long work, int per_block) {
 }
 
 void launch_bounds(const PlanParams& p, const int* const* d_cp, const int* const* d_ri, int* d_u,
-                   unsigned char* d_bin, int* d_colcnt, int* d_hist, PlanSummary* d_sum, hipStream_t s) {
+                   unsigned char* d_bin, int* d_colcnt, int* d_hist, int* d_cpt, PlanSummary* d_sum, hipStream_t s) {
   const unsigned grid = p.n == 0 ? 1u : grid_for(p.n, PLAN_THREADS);
-  k_bounds<<<grid, PLAN_THREADS, 0, s>>>(p, d_cp, d_ri, d_u, d_bin, d_colcnt, d_hist, d_sum);
+  k_bounds<<<grid, PLAN_THREADS, 0, s>>>(p, d_cp, d_ri, d_u, d_bin, d_colcnt, d_hist, d_cpt, d_sum);
 }
 
 void launch_put_ptrs(const void* const* host_ptrs, int count, const void** d_dst, PlanSummary* d_sum,

@@ -15,8 +15,10 @@ struct PtrChunk {
 
 void launch_put_ptrs(const void* const* host_ptrs, int count, const void** d_dst, PlanSummary* d_sum,
                      void* d_dummy, hipStream_t s);
+// d_cpt: (n + 1) cpt_stride(k) ints that receive the colptr arrays column by column, or
+// nullptr.
 void launch_bounds(const PlanParams& p, const int* const* d_cp, const int* const* d_ri, int* d_u,
-                   unsigned char* d_bin, int* d_colcnt, int* d_hist, PlanSummary* d_sum, hipStream_t s);
+                   unsigned char* d_bin, int* d_colcnt, int* d_hist, int* d_cpt, PlanSummary* d_sum, hipStream_t s);
 void launch_validate(const PlanParams& p, const int* const* d_cp, const int* const* d_ri, PlanSummary* d_sum,
                      hipStream_t s);
 // d_binoff holds 2 NBINS + 1 ints: offsets (NBINS + 1), then the merge map.

@@ -56,6 +56,47 @@ namespace {
     }                                                                                          \
   } while (0)
 
+// Events, recycled: timing events for SPKADD_FLAG_TRACE (two hipEventRecord calls
+// per traced launch) and plain events for host waits.
+class EventPool {
+ public:
+  static EventPool& get() {
+    static EventPool* p = new EventPool(0u);
+    return *p;
+  }
+  static EventPool& plain() {
+    static EventPool* p = new EventPool(hipEventDisableTiming);
+    return *p;
+  }
+  explicit EventPool(unsigned flags) : flags_(flags) {}
+  hipEvent_t take() {
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      if (!free_.empty()) {
+        hipEvent_t e = free_.back();
+        free_.pop_back();
+        return e;
+      }
+    }
+    hipEvent_t e = nullptr;
+    if (hipEventCreateWithFlags(&e, flags_) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    return e;
+  }
+  void give(hipEvent_t e) {
+    if (!e) return;
+    std::lock_guard<std::mutex> lk(mu_);
+    free_.push_back(e);
+  }
+
+ private:
+  unsigned flags_;
+  std::mutex mu_;
+  std::vector<hipEvent_t> free_;
+};
+
 // ---------------------------------------------------------------------------
 // Workspace cache.  Blocks are kept per device and size class (power of two,
 // at least 4 KiB).  A freed block is reused at once on the stream that freed it
@@ -89,7 +130,7 @@ class WorkspaceCache {
         bool ok = b.stream == stream;
         if (!ok && b.done) ok = block_idle(b);
         if (ok) {
-          if (b.done) (void)hipEventDestroy(b.done);
+          EventPool::plain().give(b.done);
           lst.erase(lst.begin() + (long)t);
           *out = b.ptr;
           return hipSuccess;
@@ -106,13 +147,9 @@ class WorkspaceCache {
   }
   void release(void* p, size_t bytes, int dev, hipStream_t stream) {
     if (!p) return;
-    CachedBlock b{p, stream, nullptr};
-    if (hipEventCreateWithFlags(&b.done, hipEventDisableTiming) == hipSuccess) {
-      if (hipEventRecord(b.done, stream) != hipSuccess) {
-        (void)hipEventDestroy(b.done);
-        b.done = nullptr;
-      }
-    } else {
+    CachedBlock b{p, stream, EventPool::plain().take()};
+    if (b.done && hipEventRecord(b.done, stream) != hipSuccess) {
+      EventPool::plain().give(b.done);
       b.done = nullptr;
     }
     std::lock_guard<std::mutex> lk(mu_);
@@ -127,7 +164,7 @@ class WorkspaceCache {
       for (size_t t = 0; t < lst.size();) {
         CachedBlock b = lst[t];
         if (!b.done || block_idle(b)) {
-          if (b.done) (void)hipEventDestroy(b.done);
+          EventPool::plain().give(b.done);
           (void)hipFree(b.ptr);
           lst.erase(lst.begin() + (long)t);
         } else {
@@ -193,47 +230,6 @@ class PinnedPool {
   std::vector<void*> free_;
 };
 
-// Events, recycled: timing events for SPKADD_FLAG_TRACE (two hipEventRecord calls
-// per traced launch) and plain events for host waits.
-class EventPool {
- public:
-  static EventPool& get() {
-    static EventPool* p = new EventPool(0u);
-    return *p;
-  }
-  static EventPool& plain() {
-    static EventPool* p = new EventPool(hipEventDisableTiming);
-    return *p;
-  }
-  explicit EventPool(unsigned flags) : flags_(flags) {}
-  hipEvent_t take() {
-    {
-      std::lock_guard<std::mutex> lk(mu_);
-      if (!free_.empty()) {
-        hipEvent_t e = free_.back();
-        free_.pop_back();
-        return e;
-      }
-    }
-    hipEvent_t e = nullptr;
-    if (hipEventCreateWithFlags(&e, flags_) != hipSuccess) {
-      (void)hipGetLastError();
-      return nullptr;
-    }
-    return e;
-  }
-  void give(hipEvent_t e) {
-    if (!e) return;
-    std::lock_guard<std::mutex> lk(mu_);
-    free_.push_back(e);
-  }
-
- private:
-  unsigned flags_;
-  std::mutex mu_;
-  std::vector<hipEvent_t> free_;
-};
-
 struct TraceRec {
   const char* name;
   hipEvent_t a, b;
@@ -262,6 +258,7 @@ struct spkadd_plan_s {
   const int** d_ri = nullptr;
   const void** d_va = nullptr;
   // per-column data
+  int* d_cpt = nullptr;  // the colptr arrays column by column (KArgs::cpt)
   int* d_u = nullptr;
   unsigned char* d_bin = nullptr;
   int* d_colcnt = nullptr;
@@ -403,6 +400,10 @@ constexpr int kManyCols = 64;
 // Longest column of one workgroup of 1024 threads (two share a CU's LDS).
 constexpr int kG3MaxF32 = 8192, kG3MaxF64 = 6144;
 constexpr int kMaxCap = 8192;
+// The column-by-column copy of the column pointers (k_bounds): from this many inputs on,
+// and up to 1 GiB of it.
+constexpr int kColTableMinK = 4;
+constexpr size_t kColTableMax = (size_t)1 << 28;
 constexpr float kDefaultAlphaSym = 0.5f;
 constexpr float kDefaultAlphaNum = 0.5f;
 constexpr float kDefaultFill = 0.75f;
@@ -445,6 +446,7 @@ spkadd_status check_lds(spkadd_plan_s* p) {
 KArgs base_args(const spkadd_plan_s* p) {
   KArgs a{};
   a.cp = p->d_cp;
+  a.cpt = p->d_cpt;
   a.ri = p->d_ri;
   a.va = p->d_va;
   a.m = p->m;
@@ -1004,8 +1006,20 @@ spkadd_status plan_build(spkadd_plan_s* p, int32_t m, int32_t n, int32_t k, cons
     const size_t o_list = carve((size_t)n * 4), o_sum = carve(sizeof(PlanSummary));
     const size_t o_wfirst = carve(((size_t)n + 1) * 4), o_scan = carve(scan_tmp_bytes(n));
     const size_t o_dummy = carve(4096);
+    // the column-by-column copy of the column pointers; without room for it the kernels
+    // read the inputs' own arrays
+    const size_t fixed = off, table = ((size_t)n + 1) * (size_t)cpt_stride(k);
+    bool use_table = !p->region_mode && k >= kColTableMinK && table <= kColTableMax;
+    const size_t o_cpt = use_table ? carve(table * 4) : 0;
     char* arena = nullptr;
-    if ((st = p->alloc(&arena, off, stream))) return fail(st);
+    st = p->alloc(&arena, off, stream);
+    if (st != SPKADD_OK && use_table) {
+      use_table = false;
+      g_last_error.clear();
+      st = p->alloc(&arena, fixed, stream);
+    }
+    if (st) return fail(st);
+    if (use_table) p->d_cpt = (int*)(arena + o_cpt);
     p->d_cp = (const int**)(arena + o_ptrs);
     p->d_ri = p->d_cp + k;
     p->d_va = (const void**)(p->d_ri + k);
@@ -1051,7 +1065,7 @@ spkadd_status plan_build(spkadd_plan_s* p, int32_t m, int32_t n, int32_t k, cons
   }
   {
     TraceScope t(p, "bounds", stream);
-    launch_bounds(p->pp, p->d_cp, p->d_ri, p->d_u, p->d_bin, p->d_colcnt, p->d_hist, p->d_sum, stream);
+    launch_bounds(p->pp, p->d_cp, p->d_ri, p->d_u, p->d_bin, p->d_colcnt, p->d_hist, p->d_cpt, p->d_sum, stream);
   }
   {
     TraceScope t(p, "bin_scan", stream);

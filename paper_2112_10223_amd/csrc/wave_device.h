@@ -105,14 +105,17 @@ __device__ __forceinline__ void issue_unit_loads(const KArgs& a, unsigned char* 
 // Column pointers of unit column j: a lane reads colptr_i[j], colptr_i[j+1] of its
 // inputs i; lanes 0 and 1 also read colptr(B)[j], colptr(B)[j+1] for the numeric pass.
 // Places past the last input hold its pointer and so repeat its reads.
+// cpp holds the places of column 0, a.cpt's columns being cpt_stride(k) ints apart.
 template <bool NUM, int KC>
 __device__ __forceinline__ void issue_meta_loads(const KArgs& a, const long long (&cpp)[KC], int j, int (&s)[KC],
                                                  int (&e)[KC], int& cc) {
   const int lane = lane_id();
+  const long long stride = a.cpt ? 4LL * cpt_stride(a.k) : 4LL;
+  const long long at = stride * j;
 #pragma unroll
   for (int c = 0; c < KC; ++c) {
-    s[c] = gload<int>(cpp[c] + 4LL * j);
-    e[c] = gload<int>(cpp[c] + 4LL * (j + 1));
+    s[c] = gload<int>(cpp[c] + at);
+    e[c] = gload<int>(cpp[c] + at + stride);
   }
   if (NUM) cc = gload<int>((long long)(a.colptr_c + j + (lane & 1)));
 }
@@ -695,7 +698,7 @@ __device__ __forceinline__ void run_pipe(const KArgs& a, unsigned char* base, in
 #pragma unroll
   for (int c = 0; c < KC; ++c) {
     const int li = min(lane * KC + c, a.k - 1);
-    cpp[c] = (long long)a.cp[li];
+    cpp[c] = a.cpt ? (long long)(a.cpt + li) : (long long)a.cp[li];
     rip[c] = (long long)a.ri[li];
     vap[c] = NUM ? (long long)a.va[li] : 0;
   }
