@@ -625,11 +625,16 @@ __global__ __launch_bounds__(256) void k_win_bpos_t(long long total, int k, cons
 // The ordered pass: block (c, g) takes inputs 16 g .. 16 g + 15 of window column c, a
 // wavefront one input at a time.  The boundaries are the equal row splits
 // B_q = floor(q m / P), so a row's window is arithmetic: the largest q < P with
-// q m <= (row + 1) P - 1 (a floating-point estimate, corrected by exact integer
-// compares).  Along an input the window index of its rows is kept as a running
-// maximum (so it never decreases, whatever the input), and boundary q's position is
-// the first row whose window reaches q; boundaries after the last row's window are at
+// q m <= (row + 1) P - 1.  Along an input the window index of its rows is kept as a
+// running maximum (so it never decreases, whatever the input), and boundary q's position
+// is the first row whose window reaches q; boundaries after the last row's window are at
 // the segment end.  Every boundary of the input is written once.
+//
+// Bound by its vector instructions (one row a lane): the window comes from a 32-bit
+// reciprocal and two exact 64-bit compares, and the scan of the running maximum is left
+// out where the 64 windows already ascend (always, on sorted rows).  The blocks of one
+// column, whose boundaries share cache lines, run on one XCD.  128 inputs of 2^24 x 1024
+// with 4,096 rows per column: 1187 -> 665 us.
 constexpr int WSL_THREADS = 256;
 constexpr int WSL_GROUP = 16;
 __global__ __launch_bounds__(WSL_THREADS) void k_win_search_lin(PlanParams p, const int* const* __restrict__ cp,
@@ -639,13 +644,18 @@ __global__ __launch_bounds__(WSL_THREADS) void k_win_search_lin(PlanParams p, co
                                                                 const int* __restrict__ wlin,
                                                                 int* __restrict__ bpos) {
   const int groups = (p.k + WSL_GROUP - 1) / WSL_GROUP;
-  const int c = blockIdx.x / groups, g = blockIdx.x - c * groups;
+  const int blk = xcd_remap(blockIdx.x, gridDim.x);
+  const int c = blk / groups, g = blk - c * groups;
   if (!wlin[c]) return;  // k_win_locate's column
   const int j = wcols[c];
   const int first = wfirst[c] + c;
   const int P = wfirst[c + 1] - wfirst[c];
-  const long long k = p.k, m = p.m;
-  const double inv_m = 1.0 / (double)m;
+  const long long k = p.k;
+  const unsigned m = (unsigned)p.m;
+  // rc = floor(2^32 P / m) (P <= m; P = m only when every row is a window: no more than
+  // 2^32 - 1): floor(row rc / 2^32) is the window or at most two below it
+  const unsigned long long rq = ((unsigned long long)(unsigned)P << 32) / m;
+  const unsigned rc = rq > 0xffffffffull ? 0xffffffffu : (unsigned)rq;
   const int lane = lane_id();
   const int i1 = min(p.k, (g + 1) * WSL_GROUP);
   for (int i = g * WSL_GROUP + (threadIdx.x >> 6); i < i1; i += WSL_THREADS / 64) {
@@ -657,24 +667,38 @@ __global__ __launch_bounds__(WSL_THREADS) void k_win_search_lin(PlanParams p, co
       out[0] = s;
       out[(long long)P * k] = e;
     }
+    if (e <= s) {
+      for (int q = 1 + lane; q <= P - 1; q += 64) out[(long long)q * k] = e;
+      continue;
+    }
     int prevw = 0;  // window of the row before the chunk (0 before the first row)
-    for (int base = s; base < e; base += 64) {
-      const int idx = base + lane;
-      int w = -1;
-      if (idx < e) {
-        const long long lim = ((long long)gload<int>((long long)(r + idx)) + 1) * P - 1;
-        long long q = (long long)((double)lim * inv_m);
-        q = q < 0 ? 0 : q > P - 1 ? P - 1 : q;
-        while (q > 0 && q * m > lim) --q;
-        while (q < P - 1 && (q + 1) * m <= lim) ++q;
-        w = (int)q;
+    // (lanes past the end repeat the last row: its window, and nothing to write; the rows
+    // of the next chunks are in flight while one is placed)
+    constexpr int AHEAD = 4;
+    auto at = [&](int idx, int off) { return e - 1 - idx > off ? idx + off : e - 1; };
+    int rows[AHEAD];
+#pragma unroll
+    for (int t = 0; t < AHEAD; ++t) rows[t] = gload<int>((long long)(r + at(s, 64 * t + lane)));
+    for (int base0 = s; base0 < e; base0 += 64 * AHEAD) {
+#pragma unroll
+      for (int t = 0; t < AHEAD; ++t) {
+        const int base = base0 + 64 * t;
+        if (base >= e) break;  // (uniform)
+        const int idx = base + lane;
+        const unsigned row = min((unsigned)rows[t], m - 1u);
+        rows[t] = gload<int>((long long)(r + at(base, 64 * AHEAD + lane)));
+        const unsigned long long lim = (unsigned long long)row * (unsigned)P + (unsigned)(P - 1);
+        int w = (int)__umulhi(row, rc);
+        const unsigned long long b1 = (unsigned long long)(unsigned)(w + 1) * m;
+        w += (b1 <= lim ? 1 : 0) + (b1 + m <= lim ? 1 : 0);
+        int wprev = __builtin_amdgcn_update_dpp(prevw, w, 0x138, 0xf, 0xf, false);  // lane - 1 (lane 0: prevw)
+        if (ballot(w < wprev) != 0) {  // rows out of order: the running maximum
+          w = max(wave_scan_max(w), prevw);
+          wprev = __builtin_amdgcn_update_dpp(prevw, w, 0x138, 0xf, 0xf, false);
+        }
+        for (int q = wprev + 1; q <= w; ++q) out[(long long)q * k] = idx;
+        prevw = readlane(w, 63);
       }
-      const int wm = max(wave_scan_max(w), prevw);
-      const int up = __shfl_up(wm, 1, 64);
-      const int wprev = lane == 0 ? prevw : up;
-      if (idx < e)
-        for (int q = wprev + 1; q <= wm; ++q) out[(long long)q * k] = idx;
-      prevw = readlane(wm, 63);
     }
     for (int q = prevw + 1 + lane; q <= P - 1; q += 64) out[(long long)q * k] = e;
   }
