@@ -47,7 +47,8 @@ constexpr int PIPE_WAVES_PER_BLOCK = 4;  // pipelined wave kernels: the wavefron
 constexpr int PLAN_THREADS = 256;
 
 // Accumulators of the pipelined wave kernels (wave_device.h).
-enum Acc : int { ACC_HASH = 0, ACC_BITMAP = 1, ACC_RANKED = 2 };
+// ACC_ORDERED (with a bitmap, numeric): values summed in input order.
+enum Acc : int { ACC_HASH = 0, ACC_BITMAP = 1, ACC_RANKED = 2, ACC_ORDERED = 4 };
 // Rows of 8192 bits of the ranked bitmap's top level, and the tallest matrix it serves
 // in two levels (with one row more it takes three; one of the two needs the largest
 // LDS slice).

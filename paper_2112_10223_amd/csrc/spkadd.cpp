@@ -833,6 +833,19 @@ void wg_bitmap_layout(const spkadd_plan_s* p, int b, bool numeric, KArgs& a) {
                        p->m, a);
 }
 
+// Whether the numeric pass of the wave bins sums in input order itself: every wave bin on
+// a bitmap in the pipelined kernels.  Otherwise, and for workgroup columns and windows,
+// the ordered pass sums again (ordered.hip).
+bool wave_ordered(const spkadd_plan_s* p) {
+  if (!(p->opts.flags & SPKADD_FLAG_ORDERED)) return false;
+  for (int b = BIN_W1; b <= BIN_W16; ++b) {
+    int nq = 0;
+    const int acc = wave_acc(p, b, nq);
+    if (acc == ACC_HASH || !wave_pipe_ok(p->k, p->alpha_num_q, acc)) return false;
+  }
+  return true;
+}
+
 // Launches the symbolic or numeric kernel of bin b.
 hipError_t launch_bin(spkadd_plan_s* p, int b, bool numeric, KArgs& a_in, hipStream_t s) {
   const int cnt = b == BIN_WIN ? p->n_windows : p->bin_count[b];
@@ -852,7 +865,10 @@ hipError_t launch_bin(spkadd_plan_s* p, int b, bool numeric, KArgs& a_in, hipStr
     return launch_bitmap_wg(b, numeric, f64, a, list, cnt, s);
   }
   int acc = 0;
-  if (layout_bin(p, b, numeric, a, acc)) return launch_wave_pipe(b, numeric, f64, acc, a, list, cnt, p->n_cu, s);
+  if (layout_bin(p, b, numeric, a, acc)) {
+    if (numeric && wave_ordered(p)) acc |= ACC_ORDERED;
+    return launch_wave_pipe(b, numeric, f64, acc, a, list, cnt, p->n_cu, s);
+  }
   return launch_hash(b, numeric, f64, a, list, cnt, s);
 }
 
@@ -1292,16 +1308,16 @@ spkadd_status spkadd_numeric(spkadd_plan_t p, const void* const* values, int32_t
     }
   }
   if (ordered && p->nnz_c > 0) {
-    // the rows are in place; every value summed again in input order: wave-bin columns
-    // (at most 1024 output entries), then workgroup-bin columns and row windows (at
-    // most window_cap)
+    // the rows are in place; every value not summed in input order yet is summed again:
+    // wave-bin columns (at most 1024 output entries), then workgroup-bin columns and row
+    // windows (at most window_cap)
     const bool f64 = p->dtype == SPKADD_F64;
     const int* wl = p->d_list + p->binoff[BIN_W1];
     const int nw = p->binoff[BIN_G1] - p->binoff[BIN_W1];
     const int* gl = p->d_list + p->binoff[BIN_G1];
     const int ng = p->binoff[BIN_WIN] - p->binoff[BIN_G1];
     TraceScope t(p, "num_ordered", stream, true);
-    hipError_t e = launch_ordered(a, wl, nw, 0, kOrderedWaveCap, f64, p->n_cu, stream);
+    hipError_t e = wave_ordered(p) ? hipSuccess : launch_ordered(a, wl, nw, 0, kOrderedWaveCap, f64, p->n_cu, stream);
     if (e == hipSuccess) e = launch_ordered(a, gl, ng, p->n_windows, p->pp.cap_in, f64, p->n_cu, stream);
     if (e != hipSuccess) {
       (void)hipGetLastError();

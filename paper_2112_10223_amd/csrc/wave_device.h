@@ -73,7 +73,7 @@ __device__ __forceinline__ void issue_unit_loads(const KArgs& a, unsigned char* 
   const int swl = (int)(unsigned)sw, swh = (int)(unsigned)(sw >> 32);
   int before = -1;  // starts in earlier chunks, minus one
   // (addresses of a few entries at a time: more of them would only cost registers)
-  constexpr int CH = lookup_group(E, ACC == ACC_RANKED);
+  constexpr int CH = lookup_group(E, (ACC & 3) == ACC_RANKED);
 #pragma unroll
   for (int t0 = 0; t0 < E; t0 += CH) {
   if (t0 > 0) __builtin_amdgcn_sched_barrier(0);
@@ -526,7 +526,13 @@ __device__ __forceinline__ int rk_sym_unit(const KArgs& a, unsigned char* base, 
 }
 
 // RK: over the ranked bitmap, whose levels all start at the slice's base.
-template <int E, typename V, bool RK>
+// ORD (SPKADD_FLAG_ORDERED): every value is the sequential sum of its terms in input
+// order.  A unit's entries are numbered input by input, 64 of them at a time in
+// ascending groups, so only entries of one group can meet in a slot out of order: of
+// the lanes still to add, the lowest of each slot (an LDS minimum) adds, until none is
+// left (one round for a group without equal rows).  Slots start at -0, to which adding
+// the first term gives that term.
+template <int E, typename V, bool RK, bool ORD>
 __device__ __forceinline__ void bm_num_unit(const KArgs& a, unsigned char* base, int u, int cnt, int o0,
                                             const int (&rows)[E], const V (&vals)[E]) {
   const int lane = lane_id();
@@ -567,18 +573,48 @@ __device__ __forceinline__ void bm_num_unit(const KArgs& a, unsigned char* base,
   bitmap_ranks<E, RK>(bm, pw, vr, rk);
   if constexpr (RK) forget_derived<E>(rk);
   wave_sync();  // the bitmap is read for the last time above
-  // entries that are not first write into per-lane sink slots 64 E + lane
+  if constexpr (ORD) {
+    constexpr int FREE = 64;  // (the rows' places hold the adding lane until the rows are stored)
 #pragma unroll
-  for (int t = 0; t < E; ++t) {
-    const int d = first[t] ? rk[t] : 64 * E + lane;
-    bv[d] = vals[t];
-    br[d] = rows[t];
+    for (int t = 0; t < E; ++t) {
+      bv[64 * t + lane] = V(-0.0);
+      br[64 * t + lane] = FREE;
+    }
+    wave_sync();
+#pragma unroll
+    for (int t = 0; t < E; ++t) {
+      bool todo = lane + 64 * t < u;
+      while (ballot(todo) != 0) {  // (uniform; every round ends its lowest lane's turn)
+        if (todo) atomicMin(&br[rk[t]], lane);
+        wave_sync();
+        const bool mine = todo && br[rk[t]] == lane;
+        wave_sync();
+        if (mine) {
+          bv[rk[t]] = bv[rk[t]] + vals[t];
+          br[rk[t]] = FREE;
+          todo = false;
+        }
+        wave_sync();
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < E; ++t)
+      if (lane + 64 * t < u) br[rk[t]] = rows[t];
+    wave_sync();
+  } else {
+    // entries that are not first write into per-lane sink slots 64 E + lane
+#pragma unroll
+    for (int t = 0; t < E; ++t) {
+      const int d = first[t] ? rk[t] : 64 * E + lane;
+      bv[d] = vals[t];
+      br[d] = rows[t];
+    }
+    wave_sync();
+#pragma unroll
+    for (int t = 0; t < E; ++t)
+      if (lane + 64 * t < u && !first[t]) lds_add_cas<V>(&bv[rk[t]], vals[t]);
+    wave_sync();
   }
-  wave_sync();
-#pragma unroll
-  for (int t = 0; t < E; ++t)
-    if (lane + 64 * t < u && !first[t]) lds_add_cas<V>(&bv[rk[t]], vals[t]);
-  wave_sync();
   write_column<E, V>(a, o0, c, br, bv);
   if (RK) wave_sync();  // (the next unit's segment table shares the region)
 }
@@ -666,7 +702,7 @@ __device__ __forceinline__ void pipe_step(const KArgs& a, unsigned char* base, i
     if constexpr (!NUM && ACC == ACC_BITMAP) clear_meta<KC>(a, base);
   }
   if constexpr (NUM && ACC != ACC_HASH) {
-    bm_num_unit<E, V, ACC == ACC_RANKED>(a, base, cur.u, cur.cnt, cur.o0, cur.rows, cur.vals);
+    bm_num_unit<E, V, (ACC & 3) == ACC_RANKED, (ACC & ACC_ORDERED) != 0>(a, base, cur.u, cur.cnt, cur.o0, cur.rows, cur.vals);
   } else if constexpr (NUM) {
     num_unit<E, V>(a, base, cur.u, cur.cnt, cur.o0, cur.rows, cur.vals);
   } else if constexpr (ACC != ACC_HASH) {

@@ -1,6 +1,7 @@
 // Wave-bin kernels of the plain (one SpKAdd) launch and their launcher, instantiated per
-// pass and value type (wave_sym.hip, wave_num_f32.hip, wave_num_f64.hip: one
-// translation unit each, so that they compile side by side).  The device code is in
+// pass and value type (wave_sym.hip, wave_num_f32.hip, wave_num_f64.hip and, with values
+// summed in input order, wave_ord_f32.hip, wave_ord_f64.hip: one translation unit each,
+// so that they compile side by side).  The device code is in
 // wave_device.h.
 #pragma once
 #include "wave_device.h"
@@ -57,31 +58,33 @@ hipError_t launch_pipe_k(const KArgs& a_in, const int* list, int n, int n_cu, hi
   return hipGetLastError();
 }
 
-template <int E, bool NUM, typename V>
+// ORD: ACC_ORDERED or 0 (hash tables: only 0).
+template <int E, bool NUM, typename V, int ORD>
 hipError_t launch_pipe_e(int acc, const KArgs& a, const int* list, int n, int n_cu, hipStream_t s) {
   if (a.k > 64) {
-    if (acc == ACC_BITMAP) return launch_pipe_k<E, NUM, V, ACC_BITMAP, 2>(a, list, n, n_cu, s);
-    if (acc == ACC_RANKED) return launch_pipe_k<E, NUM, V, ACC_RANKED, 2>(a, list, n, n_cu, s);
+    if (acc == ACC_BITMAP) return launch_pipe_k<E, NUM, V, ACC_BITMAP | ORD, 2>(a, list, n, n_cu, s);
+    if (acc == ACC_RANKED) return launch_pipe_k<E, NUM, V, ACC_RANKED | ORD, 2>(a, list, n, n_cu, s);
     return hipErrorInvalidValue;
   }
-  if (acc == ACC_BITMAP) return launch_pipe_k<E, NUM, V, ACC_BITMAP, 1>(a, list, n, n_cu, s);
-  if (acc == ACC_RANKED) return launch_pipe_k<E, NUM, V, ACC_RANKED, 1>(a, list, n, n_cu, s);
-  return launch_pipe_k<E, NUM, V, ACC_HASH, 1>(a, list, n, n_cu, s);
+  if (acc == ACC_BITMAP) return launch_pipe_k<E, NUM, V, ACC_BITMAP | ORD, 1>(a, list, n, n_cu, s);
+  if (acc == ACC_RANKED) return launch_pipe_k<E, NUM, V, ACC_RANKED | ORD, 1>(a, list, n, n_cu, s);
+  if constexpr (ORD == 0) return launch_pipe_k<E, NUM, V, ACC_HASH, 1>(a, list, n, n_cu, s);
+  return hipErrorInvalidValue;
 }
 
-template <bool NUM, typename V>
+template <bool NUM, typename V, int ORD = 0>
 hipError_t launch_pipe_t(int bin, int acc, const KArgs& a, const int* list, int n, int n_cu, hipStream_t s) {
   switch (bin) {
-    case BIN_W1: return launch_pipe_e<1, NUM, V>(acc, a, list, n, n_cu, s);
-    case BIN_W2: return launch_pipe_e<2, NUM, V>(acc, a, list, n, n_cu, s);
-    case BIN_W3: return launch_pipe_e<3, NUM, V>(acc, a, list, n, n_cu, s);
-    case BIN_W4: return launch_pipe_e<4, NUM, V>(acc, a, list, n, n_cu, s);
-    case BIN_W5: return launch_pipe_e<5, NUM, V>(acc, a, list, n, n_cu, s);
-    case BIN_W6: return launch_pipe_e<6, NUM, V>(acc, a, list, n, n_cu, s);
-    case BIN_W8: return launch_pipe_e<8, NUM, V>(acc, a, list, n, n_cu, s);
-    case BIN_W10: return launch_pipe_e<10, NUM, V>(acc, a, list, n, n_cu, s);
-    case BIN_W12: return launch_pipe_e<12, NUM, V>(acc, a, list, n, n_cu, s);
-    case BIN_W16: return launch_pipe_e<16, NUM, V>(acc, a, list, n, n_cu, s);
+    case BIN_W1: return launch_pipe_e<1, NUM, V, ORD>(acc, a, list, n, n_cu, s);
+    case BIN_W2: return launch_pipe_e<2, NUM, V, ORD>(acc, a, list, n, n_cu, s);
+    case BIN_W3: return launch_pipe_e<3, NUM, V, ORD>(acc, a, list, n, n_cu, s);
+    case BIN_W4: return launch_pipe_e<4, NUM, V, ORD>(acc, a, list, n, n_cu, s);
+    case BIN_W5: return launch_pipe_e<5, NUM, V, ORD>(acc, a, list, n, n_cu, s);
+    case BIN_W6: return launch_pipe_e<6, NUM, V, ORD>(acc, a, list, n, n_cu, s);
+    case BIN_W8: return launch_pipe_e<8, NUM, V, ORD>(acc, a, list, n, n_cu, s);
+    case BIN_W10: return launch_pipe_e<10, NUM, V, ORD>(acc, a, list, n, n_cu, s);
+    case BIN_W12: return launch_pipe_e<12, NUM, V, ORD>(acc, a, list, n, n_cu, s);
+    case BIN_W16: return launch_pipe_e<16, NUM, V, ORD>(acc, a, list, n, n_cu, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -89,5 +92,7 @@ hipError_t launch_pipe_t(int bin, int acc, const KArgs& a, const int* list, int 
 hipError_t launch_pipe_sym(int bin, int acc, const KArgs& a, const int* list, int n, int n_cu, hipStream_t s);
 hipError_t launch_pipe_f32(int bin, int acc, const KArgs& a, const int* list, int n, int n_cu, hipStream_t s);
 hipError_t launch_pipe_f64(int bin, int acc, const KArgs& a, const int* list, int n, int n_cu, hipStream_t s);
+hipError_t launch_pipe_ord_f32(int bin, int acc, const KArgs& a, const int* list, int n, int n_cu, hipStream_t s);
+hipError_t launch_pipe_ord_f64(int bin, int acc, const KArgs& a, const int* list, int n, int n_cu, hipStream_t s);
 
 }  // namespace spk

@@ -15,6 +15,9 @@ hipError_t launch_wave_pipe(int bin, bool numeric, bool f64, int acc, const KArg
                             int n_cu, hipStream_t s) {
   if (nunits <= 0) return hipSuccess;
   if (!numeric) return launch_pipe_sym(bin, acc, a, d_list, nunits, n_cu, s);
+  if (acc & ACC_ORDERED)
+    return f64 ? launch_pipe_ord_f64(bin, acc & 3, a, d_list, nunits, n_cu, s)
+               : launch_pipe_ord_f32(bin, acc & 3, a, d_list, nunits, n_cu, s);
   return f64 ? launch_pipe_f64(bin, acc, a, d_list, nunits, n_cu, s)
              : launch_pipe_f32(bin, acc, a, d_list, nunits, n_cu, s);
 }

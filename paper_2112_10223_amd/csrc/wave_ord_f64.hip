@@ -1,0 +1,10 @@
+// Wave-bin kernels: numeric pass, double values summed in input order (SPKADD_FLAG_ORDERED).
+#include "wave_kernels.h"
+
+namespace spk {
+
+hipError_t launch_pipe_ord_f64(int bin, int acc, const KArgs& a, const int* list, int n, int n_cu, hipStream_t s) {
+  return launch_pipe_t<true, double, ACC_ORDERED>(bin, acc, a, list, n, n_cu, s);
+}
+
+}  // namespace spk

@@ -135,3 +135,17 @@ def test_window_capacities(window_cap):
         ref = oracle.spkadd(b)
         for force in (-1, 1, 2):
             assert_matches(b, run_gpu(b, _opts(window_cap=window_cap, force_bin=force)), ref, exact_values=True)
+
+
+@pytest.mark.parametrize("m,k", [(500, 24), (70000, 7), (70000, 100), ((1 << 21) + 1, 64), ((1 << 27) + 1, 3), (40, 128)])
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_ordered_in_the_wave_kernels(m, k, dtype):
+    """Values summed in input order by the wave kernels (both bitmaps, one and two inputs
+    per lane, rows that most inputs share): bit-identical to the ordered oracle."""
+    from paper_2112_10223_amd import binding
+    note(f"ordered wave kernels m={m} k={k} {dtype.__name__}")
+    b = tall_batch(m, k, SIZES + [1100, 3000], dtype, False, seed=m % 1000 + k)
+    got = run_gpu(b, _opts(flags=binding.SPKADD_FLAG_ORDERED))
+    ref = oracle.spkadd_ordered(b)
+    assert np.array_equal(got[0], ref.colptr) and np.array_equal(got[1], ref.rowidx)
+    assert np.array_equal(got[2], ref.val.astype(dtype))
