@@ -48,7 +48,8 @@ WORKLOADS = {
 WAVE_E = [1, 2, 3, 4, 5, 6, 8, 10, 12, 16]
 
 
-def kernel_of_column(u: np.ndarray, cap: int, wave_max: int = 1024, merge: bool = True) -> np.ndarray:
+def kernel_of_column(u: np.ndarray, cap: int, wave_max: int = 1024, merge: bool = True,
+                     g3_max: int | None = None) -> np.ndarray:
     """Name of the numeric kernel each column goes to under the default options
     (mirrors the library's binning by u_j, and its merging of two adjacent
     populous wave bins)."""
@@ -71,7 +72,9 @@ def kernel_of_column(u: np.ndarray, cap: int, wave_max: int = 1024, merge: bool 
                 prev = E
     names[(u > wave_max) & (u <= min(cap, 2048))] = "num_wg256"
     names[(u > max(wave_max, min(cap, 2048))) & (u <= cap)] = "num_wg512"
-    names[u > cap] = "num_window"
+    g3 = max(cap, g3_max or cap)
+    names[(u > cap) & (u <= g3)] = "num_wg1024"
+    names[u > g3] = "num_window"
     return names
 
 
@@ -784,7 +787,8 @@ def measure_workload(name: str, batch, steps: int, warmup: int, trace_steps: int
         u += np.diff(batch.colptr[i]).astype(np.int64)
     cnt = np.diff(colptr_c.cpu().numpy().astype(np.int64))
     cap = stats["window_cap"]
-    kern = kernel_of_column(u, cap)
+    # (under the default capacities the longest column of one workgroup is twice the window capacity)
+    kern = kernel_of_column(u, cap, g3_max=2 * cap if cap == (3072 if f64 else 4096) else cap)
     roofline = None
     num_kernels = [kname for kname in mean_ms if kname.startswith("num_") and kname != "num_ordered"]
     if not num_kernels:  # timed without events: fall back to the traced pass
