@@ -244,12 +244,12 @@ __device__ __forceinline__ void bitmap_wg_unit(const KArgs& a, unsigned char* sm
     }
     if (bad) atomicOr(a.err, ERR_INPUT);
     forget_derived<EW>(vr);
-    int bits = span;  // of the bitmap that the rows' bits (vr) index
+    unsigned bits = (unsigned)span;  // of the bitmap that the rows' bits (vr) index (up to 2^31 after ranking)
     bool fresh = true;  // the low bitmap is still clear
     unsigned* lb = top;
     for (; sh > 0; sh -= 5) {  // (uniform)
       unsigned short* lp = lb == top ? reinterpret_cast<unsigned short*>(smem + a.off_top + a.wg_top_bits / 8) : pw;
-      const int ngrp = (((bits - 1) >> sh) + 64) >> 6;
+      const int ngrp = (int)((((bits - 1u) >> sh) + 64u) >> 6);
       if (lb != top) {
         for (int w = tid; w < 8 * ((ngrp + 3) >> 2); w += NT) lb[w] = 0u;
         __syncthreads();
@@ -268,12 +268,12 @@ __device__ __forceinline__ void bitmap_wg_unit(const KArgs& a, unsigned char* sm
         in_fours(t);
         if (t < live) vr[t] = (bitmap_rank(lb, lp, vr[t] >> sh) << sh) | (vr[t] & ((1 << sh) - 1));
       }
-      bits = blocks << sh;
+      bits = (unsigned)blocks << sh;
       forget_derived<EW>(vr);
       if (lb != top) __syncthreads();  // (the next level clears this one's words)
       lb = bm;
     }
-    const int ngrp = (bits + 63) >> 6;
+    const int ngrp = (int)((bits + 63u) >> 6);
     if (!fresh) {
       for (int w = tid; w < 8 * ((ngrp + 3) >> 2); w += NT) bm[w] = 0u;
       __syncthreads();

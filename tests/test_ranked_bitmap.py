@@ -149,3 +149,16 @@ def test_ordered_in_the_wave_kernels(m, k, dtype):
     ref = oracle.spkadd_ordered(b)
     assert np.array_equal(got[0], ref.colptr) and np.array_equal(got[1], ref.rowidx)
     assert np.array_equal(got[2], ref.val.astype(dtype))
+
+
+def test_every_top_block_of_the_tallest_matrix():
+    """A workgroup column with a row in each of the 64 top blocks of a 2^31 - 2 row matrix
+    (small capacities: five levels of ranked blocks)."""
+    note("workgroup bitmap, every top block")
+    m = (1 << 31) - 2
+    col = np.minimum(np.arange(64, dtype=np.int64) * (1 << 25) + np.arange(64) * 33, m - 1).astype(np.int32)
+    rows = [np.concatenate([col[0::2], col[:3]]), np.concatenate([col[1::2], col[1:2]])]
+    cps = np.array([[0, 32, 35], [0, 32, 33]], dtype=np.int32)
+    vals = [np.arange(1, r.shape[0] + 1).astype(np.float32) for r in rows]
+    b = workloads.CSCBatch(m, 2, cps, rows, vals)
+    assert_matches(b, run_gpu(b, _opts(force_bin=1, window_cap=64)), oracle.spkadd(b), exact_values=True)
