@@ -461,7 +461,7 @@ __device__ __forceinline__ void rank_rows(const KArgs& a, unsigned char* base, i
   unsigned* bm = reinterpret_cast<unsigned*>(base);
   wave_sync();  // (the segment table read before shares the region)
 #pragma unroll
-  for (int t = 0; t < E; ++t) vr[t] = (int)min((unsigned)rows[t], (unsigned)(a.m - 1));
+  for (int t = 0; t < E; ++t) vr[t] = (int)min((unsigned)rows[t], (unsigned)max(a.m, 1) - 1u);
   int nq = a.rk_nq;
   for (int sh = a.rk_shift; sh > 0; sh -= 6) {  // (uniform)
     unsigned short* pw = reinterpret_cast<unsigned short*>(base + nq * 1024);
@@ -530,8 +530,11 @@ __device__ __forceinline__ int rk_sym_unit(const KArgs& a, unsigned char* base, 
 // order.  A unit's entries are numbered input by input, 64 of them at a time in
 // ascending groups, so only entries of one group can meet in a slot out of order: of
 // the lanes still to add, the lowest of each slot (an LDS minimum) adds, until none is
-// left (one round for a group without equal rows).  Slots start at -0, to which adding
-// the first term gives that term.
+// left (one round for a group without equal rows, at most 64).  Slots start at -0, to
+// which adding the first term gives that term.  A row outside the matrix (invalid input)
+// is reported and counts as the last of the bitmap: every rank stays below 64 E, where a
+// lane reads back the minimum it took part in.  (A rank past the LDS, whose reads give 0,
+// would leave the lanes above 0 adding for ever.)
 template <int E, typename V, bool RK, bool ORD>
 __device__ __forceinline__ void bm_num_unit(const KArgs& a, unsigned char* base, int u, int cnt, int o0,
                                             const int (&rows)[E], const V (&vals)[E]) {
@@ -545,11 +548,18 @@ __device__ __forceinline__ void bm_num_unit(const KArgs& a, unsigned char* base,
   int* br = reinterpret_cast<int*>(reinterpret_cast<unsigned char*>(bv) + 64 * (E + 1) * sizeof(V));
   const int nq = RK ? rk_low_rows(E) : a.bm_nq;
   int vr[E];  // the bits of the rows
+  if constexpr (ORD) {
+    bool bad = false;
+#pragma unroll
+    for (int t = 0; t < E; ++t) bad |= (unsigned)rows[t] >= (unsigned)a.m;
+    if (bad) atomicOr(a.err, ERR_INPUT);
+  }
   if constexpr (RK) {
     rank_rows<E>(a, base, u, rows, vr);
   } else {
 #pragma unroll
-    for (int t = 0; t < E; ++t) vr[t] = rows[t];
+    for (int t = 0; t < E; ++t) vr[t] = ORD ? (int)min((unsigned)rows[t], (unsigned)(8192 * nq) - 1u) : rows[t];
+    if constexpr (ORD) forget_derived<E>(vr);
   }
   for (int q = 0; q < nq; ++q) bm4[q * 64 + lane] = make_uint4(0u, 0u, 0u, 0u);
   wave_sync();
@@ -560,7 +570,7 @@ __device__ __forceinline__ void bm_num_unit(const KArgs& a, unsigned char* base,
     first[t] = or_bit(bm, vr[t], in) == 0u && in;
   }
   wave_sync();
-  if constexpr (RK) forget_derived<E>(vr);  // (the other bitmap is faster without, at the same residency)
+  if constexpr (RK || ORD) forget_derived<E>(vr);  // (the other bitmap is faster without, at the same residency)
   int c = bitmap_prefix(bm4, reinterpret_cast<unsigned*>(pw), nq);
   if (c != cnt) {
     if (lane == 0) atomicOr(a.err, ERR_COUNT);
@@ -571,7 +581,7 @@ __device__ __forceinline__ void bm_num_unit(const KArgs& a, unsigned char* base,
   // the row and its value there, later entries of the row add their values
   int rk[E];
   bitmap_ranks<E, RK>(bm, pw, vr, rk);
-  if constexpr (RK) forget_derived<E>(rk);
+  if constexpr (RK || ORD) forget_derived<E>(rk);
   wave_sync();  // the bitmap is read for the last time above
   if constexpr (ORD) {
     constexpr int FREE = 64;  // (the rows' places hold the adding lane until the rows are stored)
@@ -584,7 +594,8 @@ __device__ __forceinline__ void bm_num_unit(const KArgs& a, unsigned char* base,
 #pragma unroll
     for (int t = 0; t < E; ++t) {
       bool todo = lane + 64 * t < u;
-      while (ballot(todo) != 0) {  // (uniform; every round ends its lowest lane's turn)
+      // (uniform; every round ends its lowest lane's turn)
+      for (int round = 0; round < 64 && ballot(todo) != 0; ++round) {
         if (todo) atomicMin(&br[rk[t]], lane);
         wave_sync();
         const bool mine = todo && br[rk[t]] == lane;
@@ -599,7 +610,7 @@ __device__ __forceinline__ void bm_num_unit(const KArgs& a, unsigned char* base,
     }
 #pragma unroll
     for (int t = 0; t < E; ++t)
-      if (lane + 64 * t < u) br[rk[t]] = rows[t];
+      if (lane + 64 * t < u) br[rk[t]] = RK ? rows[t] : vr[t];
     wave_sync();
   } else {
     // entries that are not first write into per-lane sink slots 64 E + lane

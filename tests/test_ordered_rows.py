@@ -1,0 +1,49 @@
+"""SPKADD_FLAG_ORDERED in the wave kernels: rows that no plan can hold, and terms whose bits
+a sum has to keep."""
+import numpy as np
+import pytest
+import torch  # (before the library, which then shares its HIP runtime)
+
+import workloads
+from tests.gpu_util import note, to_device
+
+pytestmark = pytest.mark.gpu
+
+
+def _planned(b, dtype):
+    """An ordered plan of b with its symbolic pass done, its inputs and its output arrays (all of
+    which the numeric pass may read: the caller keeps every one of them)."""
+    from paper_2112_10223_amd import binding
+    cps, ris, vas = to_device(b)
+    plan = binding.spkadd_plan(b.m, b.n, cps, ris, binding.SPKADD_F64 if dtype == np.float64 else binding.SPKADD_F32,
+                               binding.make_opts(flags=binding.SPKADD_FLAG_ORDERED))
+    c = torch.empty(b.n + 1, dtype=torch.int32, device="cuda:0")
+    nnz = binding.spkadd_symbolic(plan, c)
+    r = torch.empty(nnz, dtype=torch.int32, device="cuda:0")
+    return plan, cps, ris, vas, c, r, torch.empty(nnz, dtype=vas[0].dtype, device="cuda:0")
+
+
+@pytest.mark.parametrize("m", [5000, 60000, 1 << 20, (1 << 27) + 1])
+@pytest.mark.parametrize("k", [6, 100])
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_rows_outside_the_matrix_are_reported(m, k, dtype):
+    """Rows overwritten between the passes by some below 0, at m and far above, one and all of a
+    column's: every numeric pass ends and the error is reported (plain and ranked bitmap, one
+    and two inputs per lane)."""
+    from paper_2112_10223_amd import binding
+    b = workloads.er(m, 400, k, 500.0 / k, seed=k, values="f64" if dtype == np.float64 else "f32")
+    bad = np.array([-1, m, m + 1, m + 8191, 8192 * ((m + 8191) // 8192), (1 << 31) - 1, -(1 << 31)], dtype=np.int64)
+    for every in (97, 1):
+        note(f"ordered, rows outside the matrix m={m} k={k} {dtype.__name__} every={every}")
+        plan, cps, ris, vas, c, r, v = _planned(b, dtype)
+        try:
+            for i, x in enumerate(ris):
+                at = torch.arange(i % 7, x.numel(), every, device="cuda:0")
+                x[at] = torch.from_numpy(bad[(np.arange(at.numel()) + i) % bad.shape[0]].astype(np.int32)).to("cuda:0")
+            binding.spkadd_numeric(plan, vas, r, v)
+            torch.cuda.synchronize()
+            with pytest.raises(binding.SpkaddError) as ei:
+                binding.spkadd_get_stats(plan)
+            assert ei.value.status == binding.SPKADD_ERR_INVALID
+        finally:
+            plan.free()
