@@ -530,8 +530,9 @@ __device__ __forceinline__ int rk_sym_unit(const KArgs& a, unsigned char* base, 
 // order.  A unit's entries are numbered input by input, 64 of them at a time in
 // ascending groups, so only entries of one group can meet in a slot out of order: of
 // the lanes still to add, the lowest of each slot (an LDS minimum) adds, until none is
-// left (one round for a group without equal rows, at most 64).  Slots start at -0, to
-// which adding the first term gives that term.  A row outside the matrix (invalid input)
+// left (one round for a group without equal rows, at most 64).  A slot's first term is
+// stored as it is (adding it to a zero would quiet a signalling NaN): a slot untouched
+// before a group can only be so in the group's first round.  A row outside the matrix (invalid input)
 // is reported and counts as the last of the bitmap: every rank stays below 64 E, where a
 // lane reads back the minimum it took part in.  (A rank past the LDS, whose reads give 0,
 // would leave the lanes above 0 adding for ever.)
@@ -584,16 +585,15 @@ __device__ __forceinline__ void bm_num_unit(const KArgs& a, unsigned char* base,
   if constexpr (RK || ORD) forget_derived<E>(rk);
   wave_sync();  // the bitmap is read for the last time above
   if constexpr (ORD) {
-    constexpr int FREE = 64;  // (the rows' places hold the adding lane until the rows are stored)
+    // (the rows' places hold the adding lane or a slot's state until the rows are stored)
+    constexpr int FREE = 64, UNTOUCHED = 65;
 #pragma unroll
-    for (int t = 0; t < E; ++t) {
-      bv[64 * t + lane] = V(-0.0);
-      br[64 * t + lane] = FREE;
-    }
+    for (int t = 0; t < E; ++t) br[64 * t + lane] = UNTOUCHED;
     wave_sync();
 #pragma unroll
     for (int t = 0; t < E; ++t) {
       bool todo = lane + 64 * t < u;
+      int state = br[rk[t]];
       // (uniform; every round ends its lowest lane's turn)
       for (int round = 0; round < 64 && ballot(todo) != 0; ++round) {
         if (todo) atomicMin(&br[rk[t]], lane);
@@ -601,10 +601,11 @@ __device__ __forceinline__ void bm_num_unit(const KArgs& a, unsigned char* base,
         const bool mine = todo && br[rk[t]] == lane;
         wave_sync();
         if (mine) {
-          bv[rk[t]] = bv[rk[t]] + vals[t];
+          bv[rk[t]] = state == UNTOUCHED ? vals[t] : bv[rk[t]] + vals[t];
           br[rk[t]] = FREE;
           todo = false;
         }
+        state = FREE;
         wave_sync();
       }
     }

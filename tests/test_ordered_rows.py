@@ -47,3 +47,46 @@ def test_rows_outside_the_matrix_are_reported(m, k, dtype):
             assert ei.value.status == binding.SPKADD_ERR_INVALID
         finally:
             plan.free()
+
+
+@pytest.mark.parametrize("m", [3000, 1 << 20])
+@pytest.mark.parametrize("k", [5, 100])
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_special_values_keep_their_bits(m, k, dtype):
+    """Zeros of both signs, subnormal numbers, infinities, quiet and signalling NaN: a single term
+    comes out as it is stored, two equal zeros as that zero, a sum with a NaN as a NaN."""
+    from paper_2112_10223_amd import binding
+    note(f"ordered, special values m={m} k={k} {dtype.__name__}")
+    bits, sign, exp, quiet = (np.uint32, 31, 0xFF << 23, 1 << 22) if dtype == np.float32 else \
+        (np.uint64, 63, 0x7FF << 52, 1 << 51)
+    special = np.array([0, 1 << sign, 1, (1 << sign) | 5, exp, exp | (1 << sign), exp | quiet | 9, exp | 1,
+                        exp | (1 << sign) | 77], dtype=bits)
+    ns = special.shape[0]
+    # column 0: every special value alone in a row of its own; column 1: each in the first and
+    # in the last input; column 2: each added to 1 from another input; the rest empty
+    rows, vals, cps = [], [], np.zeros((k, 4), np.int32)
+    for i in range(k):
+        alone = np.arange(i, ns, k, dtype=np.int32) * 7
+        twice = np.arange(ns, dtype=np.int32) * (m // ns) if i in (0, k - 1) else np.zeros(0, np.int32)
+        one = np.arange(ns, dtype=np.int32) * 3 if i in (1, 2) else np.zeros(0, np.int32)
+        rows.append(np.concatenate([alone, twice, one]))
+        v = [special[alone // 7], special[: twice.shape[0]]]
+        v.append(special[: one.shape[0]] if i == 1 else np.full(one.shape[0], dtype(1.0)).view(bits))
+        vals.append(np.concatenate(v).view(dtype))
+        cps[i] = np.cumsum([0, alone.shape[0], twice.shape[0], one.shape[0]])
+    b = workloads.CSCBatch(m, 3, cps, rows, vals)
+    plan, dcps, ris, vas, c, r, v = _planned(b, dtype)
+    try:
+        binding.spkadd_numeric(plan, vas, r, v)
+        torch.cuda.synchronize()
+        binding.spkadd_get_stats(plan)
+    finally:
+        plan.free()
+    assert c.cpu().tolist() == [0, ns, 2 * ns, 3 * ns]
+    got = v.cpu().numpy()
+    assert np.array_equal(got[:ns].view(bits), special)
+    with np.errstate(all="ignore"):
+        for part, want in ((got[ns:2 * ns], special.view(dtype) * 2), (got[2 * ns:], special.view(dtype) + dtype(1.0))):
+            nan = np.isnan(want)
+            assert np.array_equal(np.isnan(part), nan)
+            assert np.array_equal(part[~nan].view(bits), want[~nan].view(bits))
