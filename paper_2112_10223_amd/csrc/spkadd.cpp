@@ -57,18 +57,12 @@ namespace {
   } while (0)
 
 // Events, recycled: timing events for SPKADD_FLAG_TRACE (two hipEventRecord calls
-// per traced launch) and plain events for host waits.
+// per traced launch) and plain events for host waits and released workspace blocks.  An
+// event can be recorded on streams of the device it was made on only: one pool per device.
 class EventPool {
  public:
-  static EventPool& get() {
-    static EventPool* p = new EventPool(0u);
-    return *p;
-  }
-  static EventPool& plain() {
-    static EventPool* p = new EventPool(hipEventDisableTiming);
-    return *p;
-  }
-  explicit EventPool(unsigned flags) : flags_(flags) {}
+  static EventPool& timing(int dev) { return of(dev, 0u); }
+  static EventPool& plain(int dev) { return of(dev, hipEventDisableTiming); }
   hipEvent_t take() {
     {
       std::lock_guard<std::mutex> lk(mu_);
@@ -78,20 +72,43 @@ class EventPool {
         return e;
       }
     }
-    hipEvent_t e = nullptr;
-    if (hipEventCreateWithFlags(&e, flags_) != hipSuccess) {
+    int cur = dev_;
+    if (hipGetDevice(&cur) != hipSuccess || (cur != dev_ && hipSetDevice(dev_) != hipSuccess)) {
       (void)hipGetLastError();
       return nullptr;
     }
+    hipEvent_t e = nullptr;
+    if (hipEventCreateWithFlags(&e, flags_) != hipSuccess) {
+      (void)hipGetLastError();
+      e = nullptr;
+    }
+    if (cur != dev_) (void)hipSetDevice(cur);
     return e;
   }
   void give(hipEvent_t e) {
     if (!e) return;
-    std::lock_guard<std::mutex> lk(mu_);
-    free_.push_back(e);
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      if (free_.size() < kMost) {
+        free_.push_back(e);
+        return;
+      }
+    }
+    (void)hipEventDestroy(e);
   }
 
  private:
+  static constexpr size_t kMost = 256;  // events kept, the others are destroyed
+  EventPool(int dev, unsigned flags) : dev_(dev), flags_(flags) {}
+  static EventPool& of(int dev, unsigned flags) {  // (pools are never destroyed: they outlive static teardown)
+    static std::mutex* mu = new std::mutex();
+    static auto* pools = new std::map<std::pair<int, unsigned>, EventPool*>();
+    std::lock_guard<std::mutex> lk(*mu);
+    EventPool*& p = (*pools)[{dev, flags}];
+    if (!p) p = new EventPool(dev, flags);
+    return *p;
+  }
+  int dev_;
   unsigned flags_;
   std::mutex mu_;
   std::vector<hipEvent_t> free_;
@@ -130,7 +147,7 @@ class WorkspaceCache {
         bool ok = b.stream == stream;
         if (!ok && b.done) ok = block_idle(b);
         if (ok) {
-          EventPool::plain().give(b.done);
+          EventPool::plain(dev).give(b.done);
           lst.erase(lst.begin() + (long)t);
           *out = b.ptr;
           return hipSuccess;
@@ -147,9 +164,10 @@ class WorkspaceCache {
   }
   void release(void* p, size_t bytes, int dev, hipStream_t stream) {
     if (!p) return;
-    CachedBlock b{p, stream, EventPool::plain().take()};
+    CachedBlock b{p, stream, EventPool::plain(dev).take()};
     if (b.done && hipEventRecord(b.done, stream) != hipSuccess) {
-      EventPool::plain().give(b.done);
+      (void)hipGetLastError();  // (without an event the block is reused on its own stream only)
+      EventPool::plain(dev).give(b.done);
       b.done = nullptr;
     }
     std::lock_guard<std::mutex> lk(mu_);
@@ -164,7 +182,7 @@ class WorkspaceCache {
       for (size_t t = 0; t < lst.size();) {
         CachedBlock b = lst[t];
         if (!b.done || block_idle(b)) {
-          EventPool::plain().give(b.done);
+          EventPool::plain(dev).give(b.done);
           (void)hipFree(b.ptr);
           lst.erase(lst.begin() + (long)t);
         } else {
@@ -361,30 +379,30 @@ struct TraceScope {
   hipEvent_t a = nullptr;
   TraceScope(spkadd_plan_s* p_, const char* n, hipStream_t s_, bool numeric = false) : p(p_), name(n), s(s_) {
     if (!tracing(p, numeric)) return;
-    a = EventPool::get().take();
+    a = EventPool::timing(p->device).take();
     if (a && hipEventRecord(a, s) != hipSuccess) {
       (void)hipGetLastError();
-      EventPool::get().give(a);
+      EventPool::timing(p->device).give(a);
       a = nullptr;
     }
   }
   ~TraceScope() {
     if (!a) return;
-    hipEvent_t b = EventPool::get().take();
+    hipEvent_t b = EventPool::timing(p->device).take();
     if (b && hipEventRecord(b, s) == hipSuccess) {
       p->trace.push_back({name, a, b});
     } else {
       (void)hipGetLastError();
-      EventPool::get().give(a);
-      EventPool::get().give(b);
+      EventPool::timing(p->device).give(a);
+      EventPool::timing(p->device).give(b);
     }
   }
 };
 
 void clear_trace(spkadd_plan_s* p) {
   for (auto& t : p->trace) {
-    EventPool::get().give(t.a);
-    EventPool::get().give(t.b);
+    EventPool::timing(p->device).give(t.a);
+    EventPool::timing(p->device).give(t.b);
   }
   p->trace.clear();
 }
@@ -908,7 +926,7 @@ void release_all(spkadd_plan_s* p) {
   p->allocs.clear();
   if (!p->region_mode) {
     PinnedPool::get().give(p->h_sum);  // every copy into it was waited for
-    EventPool::plain().give(p->ev_sum);
+    EventPool::plain(p->device).give(p->ev_sum);
   }
   p->h_sum = nullptr;
   p->ev_sum = nullptr;
@@ -1004,7 +1022,7 @@ spkadd_status plan_build(spkadd_plan_s* p, int32_t m, int32_t n, int32_t k, cons
   } else {
     p->h_sum = (PlanSummary*)PinnedPool::get().take();
     if (!p->h_sum) return fail(set_error(SPKADD_ERR_OOM, "pinned host allocation failed"));
-    p->ev_sum = EventPool::plain().take();
+    p->ev_sum = EventPool::plain(p->device).take();
     if (!p->ev_sum) return fail(set_error(SPKADD_ERR_HIP, "event creation failed"));
   }
   memset(p->h_sum, 0, sizeof(PlanSummary));

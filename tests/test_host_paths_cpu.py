@@ -1,0 +1,84 @@
+"""The library's host code (events, workspace, stream order, size limits) against a stand-in
+HIP runtime: no GPU."""
+import pytest
+
+from tests import fake_hip
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    folder = tmp_path_factory.mktemp("fakehip")
+    return lambda code: fake_hip.run(folder, code)
+
+
+def test_the_stand_in_runs_every_path(run):
+    """A sum with wave columns, workgroup columns and row windows: the kernels of each are
+    launched and every call succeeds."""
+    out = run("""
+        BINS[3], BINS[G1], BINS[WIN], WINDOWS.value, TOTAL.value = 70, 5, 2, 9, 40
+        s = Sum(1 << 20, 77, 6)
+        st = s.all(stream(0))
+        out = [st, s.nnz.value, sorted({x[0] for x in log()})]
+    """)
+    assert out[0] == [0, 0, 0] and out[1] == 40
+    for k in ("k_bounds", "k_wave_sym_fused", "k_wave_pipe", "k_bitmap_wg", "k_win_records"):
+        assert any(k in x for x in out[2]), k
+
+
+# ---- events ----
+
+def test_events_stay_on_their_device(run):
+    """Sums on two devices in turn, whose workspace blocks and summaries take recycled events:
+    none is recorded on a stream of another device, no call fails, and freeing a plan while
+    another device is current does not mix them either."""
+    out = run("""
+        BINS[3], BINS[G1], BINS[WIN], WINDOWS.value, TOTAL.value = 70, 5, 2, 9, 40
+        st = []
+        for turn in range(4):
+            for dev in (0, 1):
+                F.hipSetDevice(dev)
+                st += Sum(1 << 20, 77, 6).all(stream(dev, turn))
+                st += Sum(1 << 20, 77, 6, flags=2).all(stream(dev, turn))
+        F.hipSetDevice(0)
+        s = Sum(1 << 20, 77, 6)
+        st += [s.plan(stream(0)), s.symbolic(stream(0)), s.numeric(stream(0))]
+        F.hipSetDevice(1)
+        st.append(s.free())
+        st += Sum(1 << 20, 77, 6).all(stream(1))
+        out = [st, F.fake_foreign_records()]
+    """)
+    assert set(out[0]) == {0} and out[1] == 0
+
+
+def test_a_release_without_its_event_leaves_no_status(run):
+    """A block whose event cannot be recorded is released all the same, and the status of the
+    failed record is not reported by the calls that follow."""
+    out = run("""
+        BINS[3], BINS[WIN], WINDOWS.value, TOTAL.value = 70, 2, 9, 40
+        s = Sum(1 << 20, 77, 6)
+        st = [s.plan(stream(0)), s.symbolic(stream(0)), s.numeric(stream(0))]
+        F.fake_fail_records(100)
+        st.append(s.free())
+        out = [st, F.fake_last_error()]
+        F.fake_fail_records(0)
+        st += Sum(1 << 20, 77, 6).all(stream(0))
+    """)
+    assert set(out[0]) == {0} and out[1] == 0
+
+
+def test_events_are_bounded(run):
+    """Many plans at once, then none: what the pool keeps is bounded, and sums that follow each
+    other make no new events."""
+    out = run("""
+        BINS[3], TOTAL.value = 70, 40
+        plans = [Sum(1000, 70, 2, flags=2) for _ in range(600)]  # (traced: several events each)
+        st = [p.plan(stream(0, i % 5)) for i, p in enumerate(plans)] + [p.free() for p in plans]
+        kept = F.fake_events()
+        for _ in range(3): st += Sum(1000, 70, 2).all(stream(0))
+        made = F.fake_events_made()
+        for _ in range(50): st += Sum(1000, 70, 2).all(stream(0))
+        out = [st, kept, F.fake_events_made() - made]
+    """)
+    assert set(out[0]) == {0}
+    assert out[1] <= 600 + 2 * 256  # (one of every cached block, and the pools')
+    assert out[2] == 0
