@@ -162,6 +162,12 @@ void spkadd_opts_default(spkadd_opts* opts);
  *            few more times for row windows) when SPKADD_FLAG_VALIDATE is set, when
  *            some rowidx pointer is NULL, and when k > 128 (k > 64 with hash tables) or
  *            load_factor_num is not 0.5 (the wave bins then take one launch each).
+ * Device workspace, held until spkadd_free (and then kept by the library for later
+ * plans): about 18 bytes per column, 24 per input, for row windows about 8 k + 64 bytes
+ * per window; and, where it pays, a copy of the colptr arrays column by column, 4 bytes
+ * per column and input (k rounded up to a multiple of 4), at most 1 GiB.  A sum that
+ * runs out of device memory gives that copy up before it reports OOM.  Every array is
+ * rounded up to a power of two of at least 4 KiB.
  * Errors: INVALID (null pointers, k < 1, negative sizes, bad option values, or
  * malformed inputs when SPKADD_FLAG_VALIDATE is set), OOM, HIP; OVERFLOW (some u_j
  * above INT32_MAX) here when the plan waits, else from spkadd_symbolic.

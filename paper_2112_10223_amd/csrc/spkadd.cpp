@@ -350,6 +350,11 @@ struct spkadd_plan_s {
     }
     void* p = nullptr;
     hipError_t e = WorkspaceCache::get().alloc(&p, bytes, device, s);
+    if (e != hipSuccess && d_cpt) {
+      (void)hipGetLastError();
+      drop_column_table(s);
+      e = WorkspaceCache::get().alloc(&p, bytes, device, s);
+    }
     if (e != hipSuccess) {
       (void)hipGetLastError();
       return set_error(SPKADD_ERR_OOM, "device allocation of %zu bytes failed: %s", bytes, hipGetErrorString(e));
@@ -357,6 +362,19 @@ struct spkadd_plan_s {
     allocs.push_back({p, bytes});
     *out = (T*)p;
     return SPKADD_OK;
+  }
+  // Gives up the column-by-column copy of the column pointers (its memory is wanted for
+  // something a sum cannot do without): the launches that follow read the inputs' arrays.
+  void drop_column_table(hipStream_t s) {
+    for (size_t t = 0; t < allocs.size(); ++t) {
+      if (allocs[t].p != d_cpt) continue;
+      (void)hipStreamSynchronize(s);  // launches that read or write it (s follows the plan's stream)
+      (void)hipFree(d_cpt);
+      (void)hipGetLastError();
+      allocs.erase(allocs.begin() + (long)t);
+      break;
+    }
+    d_cpt = nullptr;
   }
   void release(void* p, hipStream_t s) {
     for (size_t t = 0; t < allocs.size(); ++t) {
@@ -1043,20 +1061,8 @@ spkadd_status plan_build(spkadd_plan_s* p, int32_t m, int32_t n, int32_t k, cons
     const size_t o_list = carve((size_t)n * 4), o_sum = carve(sizeof(PlanSummary));
     const size_t o_wfirst = carve(((size_t)n + 1) * 4), o_scan = carve(scan_tmp_bytes(n));
     const size_t o_dummy = carve(4096);
-    // the column-by-column copy of the column pointers; without room for it the kernels
-    // read the inputs' own arrays
-    const size_t fixed = off, table = ((size_t)n + 1) * (size_t)cpt_stride(k);
-    bool use_table = !p->region_mode && k >= kColTableMinK && table <= kColTableMax;
-    const size_t o_cpt = use_table ? carve(table * 4) : 0;
     char* arena = nullptr;
-    st = p->alloc(&arena, off, stream);
-    if (st != SPKADD_OK && use_table) {
-      use_table = false;
-      g_last_error.clear();
-      st = p->alloc(&arena, fixed, stream);
-    }
-    if (st) return fail(st);
-    if (use_table) p->d_cpt = (int*)(arena + o_cpt);
+    if ((st = p->alloc(&arena, off, stream))) return fail(st);
     p->d_cp = (const int**)(arena + o_ptrs);
     p->d_ri = p->d_cp + k;
     p->d_va = (const void**)(p->d_ri + k);
@@ -1070,6 +1076,14 @@ spkadd_status plan_build(spkadd_plan_s* p, int32_t m, int32_t n, int32_t k, cons
     p->d_wfirst = (int*)(arena + o_wfirst);
     p->d_scan_tmp = arena + o_scan;
     p->d_dummy = arena + o_dummy;
+  }
+  // the column-by-column copy of the column pointers, in a block of its own: without room
+  // for it the kernels read the inputs' own arrays, and it is given up again where a later
+  // allocation fails
+  const size_t table = ((size_t)n + 1) * (size_t)cpt_stride(k);
+  if (!p->region_mode && k >= kColTableMinK && table <= kColTableMax && p->alloc(&p->d_cpt, table, stream)) {
+    p->d_cpt = nullptr;
+    g_last_error.clear();
   }
   {
     int cus = 0;

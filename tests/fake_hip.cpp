@@ -35,6 +35,7 @@ std::map<const void*, void*> g_var_mem;
 std::vector<std::string> g_log;
 int g_fail_records = 0;
 long g_events = 0, g_events_made = 0, g_foreign_records = 0;
+int g_tables = 0, g_stale_tables = 0;  // launches with a copy of the column pointers; with a freed one
 struct { dim3 g, b; size_t lds; hipStream_t s; } g_call;
 
 hipError_t ret(hipError_t e) {
@@ -64,6 +65,8 @@ void fake_fail_records(int n) { g_fail_records = n; }
 long fake_events() { return g_events; }
 long fake_events_made() { return g_events_made; }
 long fake_foreign_records() { return g_foreign_records; }
+int fake_tables() { return g_tables; }
+int fake_stale_tables() { return g_stale_tables; }
 int fake_last_error() { return (int)g_last; }
 int fake_log_size() { return (int)g_log.size(); }
 const char* fake_log(int i) { return g_log[(size_t)i].c_str(); }
@@ -103,6 +106,13 @@ hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t lds, h
   if (is("k_win_scan")) (*(PlanSummary**)args[5])->n_windows = fake_windows;
   if (is("k_scan_small")) **(long long**)args[2] = fake_total;
   if (is("k_scan_apply")) **(long long**)args[5] = fake_total;
+  if (is("KArgs") && !is("batch")) {
+    const char* t = (const char*)((const spk::KArgs*)args[0])->cpt;
+    bool live = false;
+    for (auto& x : g_mem) live |= t >= (const char*)x.first && t < (const char*)x.first + x.second;
+    if (t) ++g_tables;
+    if (t && !live) ++g_stale_tables;
+  }
   note(name.c_str(), s);
   return hipSuccess;
 }

@@ -108,3 +108,50 @@ def test_symbolic_on_another_stream_follows_the_plan(run, kind):
     assert log[first][0] == "wait" and launched[-1] < first
     recorded = [i for i in on(a) if log[i][0] == "record" and log[i][2] == log[first][2]]
     assert recorded and launched[-1] < recorded[-1] < first
+
+
+# ---- the copy of the column pointers ----
+
+TABLE = """
+    BINS[3], BINS[G1], BINS[WIN], WINDOWS.value, TOTAL.value = 199000, 900, 100, 120000, 40
+    s = Sum(1 << 20, 200000, 64)
+"""
+
+
+def test_a_sum_that_fits_without_the_copy_succeeds(run):
+    """Device memory for everything but the copy of the column pointers: the sum gives the copy
+    up when a later allocation fails, or does not make it, and no launch reads it afterwards."""
+    peak, tables = run(TABLE + """
+    st = s.all(stream(0))
+    assert st == [0, 0, 0]
+    out = [F.fake_peak(), F.fake_tables()]
+    """)
+    table = 1 << (200001 * 64 * 4 - 1).bit_length()
+    assert tables > 0 and peak > 2 * table
+    for limit in (peak - 4096, peak - table // 2, peak - table, table // 2):
+        got = run(TABLE + f"""
+    F.fake_limit({limit})
+    st = s.all(stream(0))
+    out = [st, F.fake_stale_tables(), s.message]
+    """)
+        assert got[1] == 0
+        if limit >= peak - table:
+            assert got[0] == [0, 0, 0], (limit, got)
+        else:  # (the row windows alone need more)
+            assert got[0] == [0, 2], got
+
+
+def test_no_copy_above_its_limit(run):
+    """More column pointers than the copy may hold (1 GiB): the kernels read the inputs' arrays;
+    at the limit no more than 1 GiB is taken for it."""
+    out = run("""
+        BINS[3], TOTAL.value = 100, 40
+        big, most = Sum(1000, (1 << 28) // 64, 64), Sum(1000, (1 << 28) // 64 - 1, 64)
+        st = big.all(stream(0))
+        out = [F.fake_tables(), F.fake_peak()]
+        F.fake_peak_reset()
+        st += most.all(stream(0))
+        out += [F.fake_tables(), F.fake_peak() - out[1], st]
+    """)
+    assert set(out[4]) == {0}
+    assert out[0] == 0 and out[2] > 0 and out[3] <= 1 << 30
