@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -118,12 +119,27 @@ class EventPool {
 // Workspace cache.  Blocks are kept per device and size class (power of two,
 // at least 4 KiB).  A freed block is reused at once on the stream that freed it
 // (stream order makes that safe) and on another stream once an event recorded at
-// free time has completed.
+// free time has completed.  Blocks freed together share one event (recording one costs
+// the host about 4 us).
 // ---------------------------------------------------------------------------
+struct ReleaseEvent {
+  hipEvent_t ev;
+  int dev;
+  ReleaseEvent(int d, hipStream_t stream) : ev(EventPool::plain(d).take()), dev(d) {
+    if (ev && hipEventRecord(ev, stream) != hipSuccess) {
+      (void)hipGetLastError();  // (without an event a block is reused on its own stream only)
+      EventPool::plain(dev).give(ev);
+      ev = nullptr;
+    }
+  }
+  ReleaseEvent(const ReleaseEvent&) = delete;
+  ~ReleaseEvent() { EventPool::plain(dev).give(ev); }
+};
+
 struct CachedBlock {
   void* ptr;
   hipStream_t stream;
-  hipEvent_t done;
+  std::shared_ptr<ReleaseEvent> done;
 };
 
 class WorkspaceCache {
@@ -143,13 +159,10 @@ class WorkspaceCache {
       std::lock_guard<std::mutex> lk(mu_);
       auto& lst = free_[{dev, cls}];
       for (size_t t = 0; t < lst.size(); ++t) {
-        CachedBlock b = lst[t];
-        bool ok = b.stream == stream;
-        if (!ok && b.done) ok = block_idle(b);
-        if (ok) {
-          EventPool::plain(dev).give(b.done);
-          lst.erase(lst.begin() + (long)t);
+        const CachedBlock& b = lst[t];
+        if (b.stream == stream || (b.done->ev && block_idle(b))) {
           *out = b.ptr;
+          lst.erase(lst.begin() + (long)t);
           return hipSuccess;
         }
       }
@@ -162,16 +175,10 @@ class WorkspaceCache {
     }
     return e;
   }
-  void release(void* p, size_t bytes, int dev, hipStream_t stream) {
+  void release(void* p, size_t bytes, int dev, hipStream_t stream, const std::shared_ptr<ReleaseEvent>& done) {
     if (!p) return;
-    CachedBlock b{p, stream, EventPool::plain(dev).take()};
-    if (b.done && hipEventRecord(b.done, stream) != hipSuccess) {
-      (void)hipGetLastError();  // (without an event the block is reused on its own stream only)
-      EventPool::plain(dev).give(b.done);
-      b.done = nullptr;
-    }
     std::lock_guard<std::mutex> lk(mu_);
-    free_[{dev, size_class(bytes)}].push_back(b);
+    free_[{dev, size_class(bytes)}].push_back({p, stream, done});
   }
   // Frees every cached block of the device whose last use has completed.
   void trim(int dev) {
@@ -180,9 +187,8 @@ class WorkspaceCache {
       if (kv.first.first != dev) continue;
       auto& lst = kv.second;
       for (size_t t = 0; t < lst.size();) {
-        CachedBlock b = lst[t];
-        if (!b.done || block_idle(b)) {
-          EventPool::plain(dev).give(b.done);
+        const CachedBlock& b = lst[t];
+        if (!b.done->ev || block_idle(b)) {
           (void)hipFree(b.ptr);
           lst.erase(lst.begin() + (long)t);
         } else {
@@ -199,7 +205,7 @@ class WorkspaceCache {
   // will not query (one recorded while a graph capture was in progress on another
   // thread) is judged by its stream instead.
   static bool block_idle(const CachedBlock& b) {
-    hipError_t e = hipEventQuery(b.done);
+    hipError_t e = hipEventQuery(b.done->ev);
     (void)hipGetLastError();
     if (e == hipSuccess) return true;
     if (e == hipErrorNotReady) return false;
@@ -379,7 +385,7 @@ struct spkadd_plan_s {
   void release(void* p, hipStream_t s) {
     for (size_t t = 0; t < allocs.size(); ++t) {
       if (allocs[t].p == p) {
-        WorkspaceCache::get().release(p, allocs[t].bytes, device, s);
+        WorkspaceCache::get().release(p, allocs[t].bytes, device, s, std::make_shared<ReleaseEvent>(device, s));
         allocs.erase(allocs.begin() + (long)t);
         return;
       }
@@ -943,7 +949,10 @@ void release_all(spkadd_plan_s* p) {
     p->pending = false;
   }
   hipStream_t s = p->last_stream;
-  for (auto& a : p->allocs) WorkspaceCache::get().release(a.p, a.bytes, p->device, s);
+  if (!p->allocs.empty()) {
+    const auto done = std::make_shared<ReleaseEvent>(p->device, s);
+    for (auto& a : p->allocs) WorkspaceCache::get().release(a.p, a.bytes, p->device, s, done);
+  }
   p->allocs.clear();
   if (!p->region_mode) {
     PinnedPool::get().give(p->h_sum);  // every copy into it was waited for
