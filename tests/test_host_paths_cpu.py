@@ -155,3 +155,14 @@ def test_no_copy_above_its_limit(run):
     """)
     assert set(out[4]) == {0}
     assert out[0] == 0 and out[2] > 0 and out[3] <= 1 << 30
+
+
+@pytest.mark.parametrize("k,n,copied", [(5, 1 << 20, False), (6, 3071, False), (6, 3072, True), (128, 3071, False),
+                                        (128, 3072, True), (4, 1000, False)])
+def test_which_sums_copy_their_column_pointers(run, k, n, copied):
+    """Few inputs, or arrays of a few pages, are read where they are."""
+    out = run(f"""
+        BINS[3], TOTAL.value = 100, 40
+        out = [Sum(1000, {n}, {k}).all(stream(0)), F.fake_tables()]
+    """)
+    assert out[0] == [0, 0, 0] and (out[1] > 0) == copied
