@@ -25,6 +25,18 @@ __device__ __forceinline__ int classify(long long u, const PlanParams& p) {
   return u <= p.g3_max ? BIN_G3 : BIN_WIN;
 }
 
+// Calls f(x, lanes with b == x) for every bin x >= 0 that a lane of the wavefront has (most
+// wavefronts have one or two of the bins).
+template <typename F>
+__device__ __forceinline__ void for_each_bin(int b, F f) {
+  for (uint64_t todo = ballot(b >= 0); todo != 0;) {  // (uniform)
+    const int x = readlane(b, __builtin_ctzll(todo));
+    const uint64_t mk = ballot(b == x);
+    f(x, mk);
+    todo &= ~mk;
+  }
+}
+
 // The column pointers of 16 inputs (i0 ..) at column j into the column-by-column copy
 // (a row's last places past input k - 1 hold copies, unused).
 __device__ __forceinline__ void put_colptrs(int* __restrict__ cpt, int k, long long j, int i0, const int (&v)[16]) {
@@ -87,10 +99,11 @@ __global__ __launch_bounds__(PLAN_THREADS) void k_bounds(PlanParams p, const int
     bin[j] = (unsigned char)b;
     colcnt[j] = 0;
   }
-  for (int bb = 0; bb < NBINS; ++bb) {
-    const uint64_t mk = ballot(b == bb);
-    if (lane == 0) wh[w][bb] = __popcll(mk);
-  }
+  if (lane < NBINS) wh[w][lane] = 0;
+  wave_sync();
+  for_each_bin(b, [&](int x, uint64_t mk) {
+    if (lane == 0) wh[w][x] = __popcll(mk);
+  });
   const unsigned long long tot = block_sum<PLAN_THREADS>((unsigned long long)uj, red);
   if (threadIdx.x < NBINS) {
     int s = 0;
@@ -164,24 +177,24 @@ __global__ __launch_bounds__(1024) void k_bin_scan(int nblk, int merge, int* __r
       s += t < nblk ? hist[t * NBINS + b] : 0;
     }
     s = wave_total_add(s);
-    if (lane == 0) totals[b] = s;
+    if (lane == 0) {
+      totals[b] = s;
+      map[b] = b;
+    }
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int x = 0; x < NBINS; ++x) map[x] = x;
-    if (merge) {
-      long long wave_cols = 0;
-      for (int x = BIN_W1; x <= BIN_W16; ++x) wave_cols += totals[x];
-      int prev = -1;
-      for (int x = BIN_W1; x <= BIN_W16; ++x) {
-        if (totals[x] == 0) continue;
-        if (prev >= 0 && 16LL * totals[prev] >= wave_cols && 16LL * totals[x] >= wave_cols &&
-            2 * wave_bin_E(x) <= 3 * wave_bin_E(prev)) {
-          map[prev] = x;  // pairs only: x takes no further merge
-          prev = -1;
-        } else {
-          prev = x;
-        }
+  if (threadIdx.x == 0 && merge) {
+    long long wave_cols = 0;
+    for (int x = BIN_W1; x <= BIN_W16; ++x) wave_cols += totals[x];
+    int prev = -1;
+    for (int x = BIN_W1; x <= BIN_W16; ++x) {
+      if (totals[x] == 0) continue;
+      if (prev >= 0 && 16LL * totals[prev] >= wave_cols && 16LL * totals[x] >= wave_cols &&
+          2 * wave_bin_E(x) <= 3 * wave_bin_E(prev)) {
+        map[prev] = x;  // pairs only: x takes no further merge
+        prev = -1;
+      } else {
+        prev = x;
       }
     }
   }
@@ -201,16 +214,15 @@ __global__ __launch_bounds__(1024) void k_bin_scan(int nblk, int merge, int* __r
     if (lane == 0) mtot[b] = carry;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int acc = 0;
-    for (int bb = 0; bb < NBINS; ++bb) {
-      const int c = map[bb] == bb ? mtot[bb] : 0;
-      binoff[bb] = acc;
-      binoff[NBINS + 1 + bb] = map[bb];
-      sum->bin_count[bb] = c;
-      acc += c;
+  if (b == 0) {  // one lane per bin
+    const int c = lane < NBINS && map[lane] == lane ? mtot[lane] : 0;
+    const int incl = wave_scan_add(c);
+    if (lane < NBINS) {
+      binoff[lane] = incl - c;
+      binoff[NBINS + 1 + lane] = map[lane];
+      sum->bin_count[lane] = c;
     }
-    binoff[NBINS] = acc;
+    if (lane == 63) binoff[NBINS] = incl;
   }
 }
 
@@ -224,11 +236,12 @@ __global__ __launch_bounds__(PLAN_THREADS) void k_bin_scatter(PlanParams p, cons
   const int lane = lane_id(), w = threadIdx.x >> 6;
   const int b = j < p.n ? binoff[NBINS + 1 + (int)bin[j]] : -1;  // bin after merging
   int rank = 0;
-  for (int bb = 0; bb < NBINS; ++bb) {
-    const uint64_t mk = ballot(b == bb);
-    if (b == bb) rank = mbcnt(mk);
-    if (lane == 0) wc[w][bb] = __popcll(mk);
-  }
+  if (lane < NBINS) wc[w][lane] = 0;
+  wave_sync();
+  for_each_bin(b, [&](int x, uint64_t mk) {
+    if (b == x) rank = mbcnt(mk);
+    if (lane == 0) wc[w][x] = __popcll(mk);
+  });
   __syncthreads();
   if (b > BIN_EMPTY) {
     int before = 0;
