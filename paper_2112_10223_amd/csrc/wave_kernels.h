@@ -38,8 +38,14 @@ int register_blocks(F kernel) {
   return w < 1 ? 1 : w > 8 ? 8 : w;
 }
 
-// The launch fills the CUs with resident wavefronts (as many as LDS and registers
-// hold), and each takes an equal share of the units, at most 64.
+// The launch fills the CUs with resident wavefronts and each takes an equal share of the
+// units, at most 64.  With more than four workgroups on a CU a wavefront of a short launch
+// would get one or two units, and nothing of the next one in flight while it works: as
+// many as LDS and registers hold only where each then still has three units (two at
+// E = 1).  Numeric fp32, 4,000 rows, at most four / all: u = 128, 6,000 columns 11.7 /
+// 14.9 us, 16,000 16.8 / 20.1, 64,000 37.2 / 36.4; u = 192, 6,000 columns 14.4 / 18.4,
+// 65,536 rows, 130,000 columns 128.8 / 127.4; u = 32, 8,000 columns 8.4 / 9.4, 16,000
+// 10.6 / 10.6, 130,000 40.3 / 36.1.
 template <int E, bool NUM, typename V, int ACC, int KC>
 hipError_t launch_pipe_k(const KArgs& a_in, const int* list, int n, int n_cu, hipStream_t s) {
   static_assert(PIPE_WAVES_PER_BLOCK == 4, "register_blocks counts one wavefront per SIMD");
@@ -49,7 +55,9 @@ hipError_t launch_pipe_k(const KArgs& a_in, const int* list, int n, int n_cu, hi
   int bpc = (int)((size_t)max_lds_bytes() / lds);
   if (bpc > by_regs) bpc = by_regs;
   if (bpc < 1) bpc = 1;
-  const long long resident = (long long)n_cu * bpc * PIPE_WAVES_PER_BLOCK;
+  const long long per_block = (long long)n_cu * PIPE_WAVES_PER_BLOCK;
+  if (bpc > 4 && n <= per_block * bpc * (E == 1 ? 1 : 2)) bpc = 4;
+  const long long resident = per_block * bpc;
   const long long upw = (n + resident - 1) / resident;
   a.upw = (int)(upw < 1 ? 1 : upw > 64 ? 64 : upw);
   const int waves = (n + a.upw - 1) / a.upw;
