@@ -101,6 +101,10 @@ __device__ __forceinline__ int build_meta(const KArgs& a, int j, bool win, int b
       if (win) {
         s = a.bpos[(long long)blo * a.k + i];
         e = max(a.bpos[(long long)(blo + 1) * a.k + i], s);  // (only an unsorted input could invert them)
+      } else if (a.cpt) {
+        const int* c = a.cpt + (long long)j * cpt_stride(a.k) + i;
+        s = c[0];
+        e = c[cpt_stride(a.k)];
       } else {
         const int* c = a.cp[i];
         s = c[j];
