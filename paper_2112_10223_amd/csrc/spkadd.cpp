@@ -326,9 +326,9 @@ struct spkadd_plan_s {
   // the plan's summary copy is queued but not yet waited for (spkadd_symbolic waits)
   bool pending = false;
   hipStream_t plan_stream = nullptr;
-  // ev_sum was recorded behind the plan's last launch on plan_stream, and no pass has
-  // followed yet
-  bool plan_event = false;
+  // no pass has followed the plan yet; ev_sum was recorded behind the plan's last launch on
+  // plan_stream (else only the column lists may still be being built there)
+  bool fresh = false, plan_event = false;
   // trace
   std::vector<TraceRec> trace;
   // region mode (the no-allocation entry point): every workspace array is carved
@@ -1160,7 +1160,7 @@ spkadd_status plan_build(spkadd_plan_s* p, int32_t m, int32_t n, int32_t k, cons
     if ((st = copy_summary(p, stream))) return fail(st);  // (its event also covers the column lists)
     p->pending = true;
     p->plan_stream = stream;
-    p->plan_event = true;
+    p->fresh = p->plan_event = true;
     return SPKADD_OK;
   }
   // the host needs the bin counts; the column lists are built while it waits
@@ -1171,9 +1171,10 @@ spkadd_status plan_build(spkadd_plan_s* p, int32_t m, int32_t n, int32_t k, cons
   }
   if ((e = hipGetLastError())) return hipfail(e, "plan kernels");
   if ((st = plan_finish(p, stream))) return st;
-  if (!p->region_mode) {  // the column lists and window records are still being built
+  p->plan_stream = stream;
+  p->fresh = true;
+  if (p->n_wcols > 0 && !p->region_mode) {  // the window records are still being built
     if ((e = hipEventRecord(p->ev_sum, stream))) return hipfail(e, "event record");
-    p->plan_stream = stream;
     p->plan_event = true;
   }
   return SPKADD_OK;
@@ -1259,12 +1260,19 @@ spkadd_status spkadd_symbolic(spkadd_plan_t p, int32_t* colptr_c, int64_t* nnz_c
   KArgs a = base_args(p);
   a.alpha_q = p->alpha_sym_q;
   bool wave_done = false;
-  if (p->plan_event && stream != p->plan_stream && hipStreamWaitEvent(stream, p->ev_sum, 0) != hipSuccess) {
-    (void)hipGetLastError();
-    p->failed = true;
-    return set_error(SPKADD_ERR_HIP, "stream wait on the plan failed");
+  if (p->fresh && stream != p->plan_stream) {
+    if (!p->plan_event) {
+      // the lists once more, behind which this pass runs: the bins they come from are
+      // complete (the plan waited for them), and both launches write the same ids
+      // (an event behind the plan's launch would cost every plan 1.2 us)
+      launch_bin_scatter(p->pp, p->d_bin, p->d_hist, p->d_binoff, p->d_list, stream);
+    } else if (hipStreamWaitEvent(stream, p->ev_sum, 0) != hipSuccess) {
+      (void)hipGetLastError();
+      p->failed = true;
+      return set_error(SPKADD_ERR_HIP, "stream wait on the plan failed");
+    }
   }
-  p->plan_event = false;  // (this call waits for its own work, and with it for the plan's)
+  p->fresh = p->plan_event = false;  // (this call waits for its own work, and with it for the plan's)
   if (p->pending) {
     // the wave bins first, from the device's bin lists; then the plan's wait
     KArgs fa = a;
