@@ -1070,9 +1070,13 @@ spkadd_status plan_build(spkadd_plan_s* p, int32_t m, int32_t n, int32_t k, cons
     };
     const size_t o_ptrs = carve(3 * (size_t)k * sizeof(void*));
     const size_t o_u = carve((size_t)n * 4), o_bin = carve((size_t)n), o_colcnt = carve((size_t)n * 4);
-    const size_t o_hist = carve((size_t)nblk * NBINS * 4), o_binoff = carve((2 * NBINS + 1) * 4);
+    // (in the fixed region, whose calls run on one stream, the window numbers follow in the
+    // place of the bin histograms, which the column lists were built from)
+    const size_t hist = (size_t)nblk * NBINS * 4, wfirst = ((size_t)n + 1) * 4;
+    const size_t o_hist = carve(p->region_mode && wfirst > hist ? wfirst : hist);
+    const size_t o_binoff = carve((2 * NBINS + 1) * 4);
     const size_t o_list = carve((size_t)n * 4), o_sum = carve(sizeof(PlanSummary));
-    const size_t o_wfirst = carve(((size_t)n + 1) * 4), o_scan = carve(scan_tmp_bytes(n));
+    const size_t o_wfirst = p->region_mode ? o_hist : carve(wfirst), o_scan = carve(scan_tmp_bytes(n));
     const size_t o_dummy = carve(4096);
     char* arena = nullptr;
     if ((st = p->alloc(&arena, off, stream))) return fail(st);

@@ -170,3 +170,29 @@ def test_which_sums_copy_their_column_pointers(run, k, n, copied):
         out = [Sum(1000, {n}, {k}).all(stream(0)), F.fake_tables()]
     """)
     assert out[0] == [0, 0, 0] and (out[1] > 0) == copied
+
+
+# ---- the no-allocation call's static array ----
+
+def test_noalloc_takes_as_many_columns_as_before(run):
+    """The largest sum without row windows that fitted the 64 MiB with fourteen bins fits with the
+    bins there are now; one of 3% more columns does not, and says so."""
+    out = run("""
+        SCRATCH, TILE, THREADS = 64 << 20, None, 256
+        def need(n, k, bins, tile):
+            r = lambda x: (x + 255) // 256 * 256
+            blocks = (n + THREADS - 1) // THREADS
+            return (r(24 * k) + 3 * r(4 * n) + r(n) + r(4 * blocks * bins) + r(4 * (2 * bins + 1)) + r(96) +
+                    r(4 * (n + 1)) + r(8 * ((n + tile - 1) // tile + 1)) + 4096)
+        out = []
+        BINS[3], TOTAL.value = 100, 40
+        for k in (1, 4, 300):
+            lo, hi = 1, 1 << 23
+            while lo < hi:
+                mid = (lo + hi + 1) // 2
+                if need(mid, k, 14, 4096) <= SCRATCH: lo = mid
+                else: hi = mid - 1
+            out.append([lo, Sum(1000, lo, k).noalloc(stream(0)), Sum(1000, lo + lo // 32, k).noalloc(stream(0))])
+    """)
+    for n, fits, more in out:
+        assert n > 3500000 and (fits, more) == (0, 6)
