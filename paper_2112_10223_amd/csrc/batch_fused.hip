@@ -72,7 +72,7 @@ __global__ __launch_bounds__(64 * PIPE_WAVES_PER_BLOCK, NUM ? 2 : 4) void k_batc
 template <int THREADS, bool NUM, typename V>
 __global__ __launch_bounds__(THREADS, (NUM && sizeof(V) == 8 ? 3 : 4)) void k_batch_wg(BatchArgs b, KArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ int red[2 * (THREADS / 64) + 1];
+  __shared__ int red[bitmap_wg_reds(THREADS)];
   const int count = b.slotoff[BSLOTS + 1 + BSLOT_WG];
   const int off = b.slotoff[BSLOT_WG];
   for (int item = xcd_remap(blockIdx.x, gridDim.x); item < count; item += gridDim.x) {

@@ -18,7 +18,7 @@ namespace spk {
 template <int NT, int EW, bool NUM, bool WIN, typename V>
 __global__ __launch_bounds__(NT, 8) void k_bitmap_wg(KArgs a, const int* __restrict__ list, int nunits) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ int red[2 * (NT / 64) + 1];
+  __shared__ int red[bitmap_wg_reds(NT)];
   const int unit = xcd_remap(blockIdx.x, gridDim.x);
   if (unit >= nunits) return;  // uniform over the block
   int j, blo = 0, rlo = 0, rhi = a.m;

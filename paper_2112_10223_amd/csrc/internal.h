@@ -151,6 +151,10 @@ void lds_layout_pipe(int bin, bool numeric, int vbytes, int ts_max, int acc, int
 // units (G1, G2, G3 or WIN).
 void lds_layout_bitmap_wg(bool numeric, int vbytes, int k, int cap, int regs, int span, KArgs& a);
 int bitmap_wg_threads(int bin, int cap);
+// LDS of the workgroup kernels' own arrays (their reductions'), beside the layouts'.
+constexpr int bitmap_wg_reds(int threads) { return 2 * (threads / 64) + 1; }
+constexpr int bitmap_wg_own_lds(int threads) { return (4 * bitmap_wg_reds(threads) + 15) & ~15; }
+constexpr int hash_wg_own_lds(int threads) { return (8 * (threads / 64 + 1) + 4 + 15) & ~15; }
 hipError_t launch_bitmap_wg(int bin, bool numeric, bool f64, const KArgs& a, const int* d_list, int nunits,
                             hipStream_t s);
 // upw (units per wavefront) is set by the launcher from the wavefronts that can be resident.

@@ -465,6 +465,7 @@ int ktop_of(int k) {
   return t;
 }
 
+bool is_wave(int b) { return b >= BIN_W1 && b <= BIN_W16; }
 bool layout_bin(const spkadd_plan_s* p, int b, bool numeric, KArgs& a, int& acc);
 bool wg_bitmap_bin(const spkadd_plan_s* p, int b);
 void wg_bitmap_layout(const spkadd_plan_s* p, int b, bool numeric, KArgs& a);
@@ -481,7 +482,9 @@ spkadd_status check_lds(spkadd_plan_s* p) {
       long long bytes = (long long)a.slice_bytes * (pipe ? PIPE_WAVES_PER_BLOCK : bin_units_per_block(b));
       if (wg_bitmap_bin(p, b)) {
         wg_bitmap_layout(p, b, numeric != 0, a);
-        bytes = a.slice_bytes;
+        bytes = a.slice_bytes + bitmap_wg_own_lds(bitmap_wg_threads(b, a.wg_cap));
+      } else if (!is_wave(b)) {
+        bytes += hash_wg_own_lds(b == BIN_G1 ? G1_THREADS : G2_THREADS);
       }
       if (bytes > lmax)
         return set_error(SPKADD_ERR_UNSUPPORTED,
@@ -831,8 +834,6 @@ spkadd_status build_windows_unsorted(spkadd_plan_s* p, hipStream_t s) {
   HIP_TRY(hipGetLastError());
   return SPKADD_OK;
 }
-
-bool is_wave(int b) { return b >= BIN_W1 && b <= BIN_W16; }
 
 // The accumulator of a wave bin: hash tables where asked for (accum_mode, or the
 // degenerate-hash test hook), the bitmap over all rows (nq rows of 256 words) where the

@@ -96,8 +96,14 @@ hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* lds, hipStream_t*
 hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t lds, hipStream_t s) {
   using spk::PlanSummary;
   const std::string& name = g_kernels[f];
-  if (lds > 160 * 1024) return ret(hipErrorInvalidValue);
   auto is = [&](const char* k) { return name.find(k) != std::string::npos; };
+  size_t fixed = 0;  // the kernel's own LDS arrays
+  for (const char* k : {"k_bitmap_wgILi", "k_hash_wgILi"})
+    if (is(k)) {
+      const size_t waves = (size_t)atoi(name.c_str() + name.find(k) + strlen(k)) / 64;
+      fixed = k[2] == 'b' ? 4 * (2 * waves + 1) : 8 * (waves + 1) + 4;
+    }
+  if (lds + (fixed + 15) / 16 * 16 > 160 * 1024) return ret(hipErrorInvalidValue);
   if (is("k_bounds") && !is("batch")) (*(PlanSummary**)args[8])->nnz_in = 1;
   if (is("k_bin_scan")) {
     PlanSummary* sum = *(PlanSummary**)args[4];

@@ -196,3 +196,27 @@ def test_noalloc_takes_as_many_columns_as_before(run):
     """)
     for n, fits, more in out:
         assert n > 3500000 and (fits, more) == (0, 6)
+
+
+# ---- on-chip memory ----
+
+@pytest.mark.parametrize("accum_mode", [0, 1])
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_the_largest_number_of_inputs_is_refused_or_runs(run, dtype, accum_mode):
+    """Around the number of inputs whose segment table just fits a workgroup's LDS (with the
+    kernels' own arrays), a sum runs or is refused as unsupported: no launch fails."""
+    out = run(f"""
+        out = []
+        for b in ([G1, G1 + 1, G3, WIN] if {accum_mode} == 0 else [G1, G1 + 1, WIN]):
+            for i in range(WIN + 1): BINS[i] = 0
+            BINS[b], WINDOWS.value, TOTAL.value = 5, 9 if b == WIN else 0, 40
+            status = lambda k: Sum(1 << 20, 70, k, {dtype}, accum_mode={accum_mode}).all(stream(0))
+            lo, hi = 1, 20000
+            while lo < hi:
+                mid = (lo + hi + 1) // 2
+                if status(mid) == [0, 0, 0]: lo = mid
+                else: hi = mid - 1
+            out.append([b, lo, sorted({{status(k)[-1] for k in range(lo - 3, lo + 24)}})])
+    """)
+    for b, most, statuses in out:
+        assert most >= 3719 and statuses == [0, 6], (b, most, statuses)
