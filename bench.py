@@ -19,6 +19,7 @@ import argparse
 import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -78,23 +79,39 @@ def kernel_of_column(u: np.ndarray, cap: int, wave_max: int = 1024, merge: bool 
     return names
 
 
-# kernel sources whose change makes a committed traffic summary stale, by trace-name prefix
+def longest_workgroup_column(u: np.ndarray, cap: int, n_window_cols: int) -> int:
+    """The most entries of a column that one workgroup takes, from the number of columns cut
+    into row windows (the longest ones)."""
+    longest = np.sort(u)[::-1]
+    return max(cap, int(longest[n_window_cols])) if n_window_cols < len(u) else cap
+
+
+# sources of a kernel (by trace-name prefix), a change of which, or of a header they
+# include, makes a committed traffic summary stale
 _KERNEL_SOURCES = {
-    "num_wave": ("hash_kernels.hip", "wave_kernels.hip", "wave_kernels.h", "wave_num_f32.hip", "wave_num_f64.hip",
-                 "wave_device.h", "hash_common.h", "device.h", "internal.h"),
-    "num_window": ("bitmap_wg.hip", "bitmap_wg_device.h", "hash_kernels.hip", "hash_common.h", "device.h",
-                   "internal.h"),
+    "num_wave": ("hash_kernels.hip", "wave_kernels.hip", "wave_num_f32.hip", "wave_num_f64.hip"),
+    "num_window": ("bitmap_wg.hip", "hash_kernels.hip"),
 }
+
+
+def kernel_sources(kernel: str) -> list:
+    """The files that the kernel is compiled from, with the headers of csrc/ they include."""
+    csrc = os.path.join(ROOT, "paper_2112_10223_amd", "csrc")
+    files = next((list(v) for key, v in _KERNEL_SOURCES.items() if kernel.startswith(key)), None)
+    if files is None:
+        return sorted(f for f in os.listdir(csrc) if f.endswith((".hip", ".h")))
+    for fn in files:  # (grows while it is walked)
+        with open(os.path.join(csrc, fn)) as f:
+            for inc in re.findall(r'^#include "([^"]+)"', f.read(), flags=re.M):
+                if inc not in files and os.path.exists(os.path.join(csrc, inc)):
+                    files.append(inc)
+    return sorted(files)
 
 
 def source_sha(kernel: str = "num_wave") -> str:
     """Hash of the sources the kernel (by trace name) is compiled from."""
-    files = next((v for key, v in _KERNEL_SOURCES.items() if kernel.startswith(key)), None)
-    if files is None:
-        files = tuple(sorted(f for f in os.listdir(os.path.join(ROOT, "paper_2112_10223_amd", "csrc"))
-                             if f.endswith((".hip", ".h"))))
     h = hashlib.sha256()
-    for fn in files:
+    for fn in kernel_sources(kernel):
         with open(os.path.join(ROOT, "paper_2112_10223_amd", "csrc", fn), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
@@ -787,8 +804,7 @@ def measure_workload(name: str, batch, steps: int, warmup: int, trace_steps: int
         u += np.diff(batch.colptr[i]).astype(np.int64)
     cnt = np.diff(colptr_c.cpu().numpy().astype(np.int64))
     cap = stats["window_cap"]
-    # (under the default capacities the longest column of one workgroup is twice the window capacity)
-    kern = kernel_of_column(u, cap, g3_max=2 * cap if cap == (3072 if f64 else 4096) else cap)
+    kern = kernel_of_column(u, cap, g3_max=longest_workgroup_column(u, cap, stats["n_window_cols"]))
     roofline = None
     num_kernels = [kname for kname in mean_ms if kname.startswith("num_") and kname != "num_ordered"]
     if not num_kernels:  # timed without events: fall back to the traced pass
