@@ -16,7 +16,10 @@
  *
  * Search: coordinate descent from the caller's opts (or the defaults) -- every value
  * of one parameter with the others fixed, keep the fastest, next parameter.  The
- * window parameters are searched only when some column is too long for a wavefront.
+ * window parameters are searched only when some column is too long for a wavefront (a
+ * window_cap other than 0 also ends the workgroup columns above it, see spkadd.h), the
+ * load factor only when columns go to hash tables (accum_mode 1 chosen before it, more
+ * than 128 inputs).
  * A trial is the whole call sequence spkadd_plan / spkadd_symbolic / spkadd_numeric /
  * spkadd_free with a stream synchronisation, timed on the host (median of `reps`
  * after one untimed run); colptr(B) of every trial is compared with the first one and

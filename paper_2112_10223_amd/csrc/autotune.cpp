@@ -530,6 +530,7 @@ spkadd_status spkadd_tune(int32_t m, int32_t n, int32_t k, const int32_t* const*
     Setter set;
     std::vector<double> values;
     bool long_only;
+    bool tables_only = false;
   };
   const std::vector<Axis> axes = {
       {[](spkadd_opts& o, double v) { o.wave_max = (int)v; }, {1024, 768, 512, 256}, false},
@@ -543,12 +544,17 @@ spkadd_status spkadd_tune(int32_t m, int32_t n, int32_t k, const int32_t* const*
        },
        {1.0, 0.5, 2.0, 4.0, -1.0}, false},
       {[](spkadd_opts& o, double v) { o.wave_merge = (int)v; }, {0, 1}, false},
-      {[](spkadd_opts& o, double v) { o.load_factor_sym = (float)v; }, {0.5, 0.35, 0.7}, false},
+      {[](spkadd_opts& o, double v) { o.load_factor_sym = (float)v; }, {0.5, 0.35, 0.7}, false, true},
       {[](spkadd_opts& o, double v) { o.window_cap = (int)v; }, {0, 1024, 2048, 4096, 6144, 8192}, true},
       {[](spkadd_opts& o, double v) { o.window_fill = (float)v; }, {0.75, 0.5, 1.0}, true},
   };
   for (const Axis& ax : axes) {
     if (ax.long_only && !long_cols) continue;
+    // (where every column is counted on bitmaps, the load factor's trials would time the same
+    // kernels, and noise choose between them)
+    const bool tables = cur.accum_mode == SPKADD_ACCUM_HASH || cur.hash_mode != 0 || k > 128 ||
+                        (cur.load_factor_num != 0.f && cur.load_factor_num != 0.5f);
+    if (ax.tables_only && !tables) continue;
     spkadd_opts axis_best = cur;
     double axis_ms = cur_ms;
     for (double v : ax.values) {

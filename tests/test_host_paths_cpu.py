@@ -220,3 +220,22 @@ def test_the_largest_number_of_inputs_is_refused_or_runs(run, dtype, accum_mode)
     """)
     for b, most, statuses in out:
         assert most >= 3719 and statuses == [0, 6], (b, most, statuses)
+
+
+# ---- the tuner ----
+
+@pytest.mark.parametrize("k", [6, 130])
+def test_the_tuner_tries_load_factors_only_where_tables_are_used(run, k):
+    """On bitmaps alone a load factor changes nothing: it is tried only with hash tables chosen
+    before it, or with more inputs than the bitmaps of a wavefront take."""
+    out = run(f"""
+        BINS[3], TOTAL.value = 70, 1
+        best, rep, trials = B.Opts(), B.TuneReport(), (B.TuneTrial * 200)()
+        ptrs = (ctypes.c_void_p * {k})(*[ADDR] * {k})
+        st = B._tune_fns().spkadd_tune(200000, 70, {k}, ptrs, ptrs, ptrs, 0, None, 1, ctypes.byref(best),
+                                       ctypes.byref(rep), trials, 200, stream(0))
+        out = [st, [(t.opts.accum_mode, round(t.opts.load_factor_sym, 2)) for t in trials[:rep.trials]]]
+    """)
+    assert out[0] == 0 and len(out[1]) >= 10
+    assert all(f == 0.0 or a == 1 or k > 128 for a, f in out[1])
+    assert k <= 128 or {0.35, 0.5, 0.7} <= {f for a, f in out[1]}
