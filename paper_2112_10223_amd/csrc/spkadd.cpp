@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <chrono>
 #include <climits>
 #include <cstdarg>
@@ -101,13 +102,21 @@ class EventPool {
  private:
   static constexpr size_t kMost = 256;  // events kept, the others are destroyed
   EventPool(int dev, unsigned flags) : dev_(dev), flags_(flags) {}
-  static EventPool& of(int dev, unsigned flags) {  // (pools are never destroyed: they outlive static teardown)
-    static std::mutex* mu = new std::mutex();
-    static auto* pools = new std::map<std::pair<int, unsigned>, EventPool*>();
-    std::lock_guard<std::mutex> lk(*mu);
-    EventPool*& p = (*pools)[{dev, flags}];
-    if (!p) p = new EventPool(dev, flags);
-    return *p;
+  // The pools in order of first use (never destroyed: they outlive static teardown).  No lock
+  // and no search tree: a sum's first pass finds its code and data in no cache, and a map
+  // cost it 5 us.
+  static EventPool& of(int dev, unsigned flags) {
+    static std::atomic<EventPool*> pools[2 * 512];
+    for (auto& at : pools) {
+      EventPool* p = at.load(std::memory_order_acquire);
+      if (!p) {
+        auto* made = new EventPool(dev, flags);
+        if (at.compare_exchange_strong(p, made)) return *made;
+        delete made;  // (p: another thread's)
+      }
+      if (p->dev_ == dev && p->flags_ == flags) return *p;
+    }
+    return *new EventPool(dev, flags);  // (more devices than a system holds)
   }
   int dev_;
   unsigned flags_;
