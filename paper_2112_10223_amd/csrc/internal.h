@@ -114,6 +114,7 @@ struct KArgs {
   int off_P, off_adj, off_adjv, off_hist, off_match, off_mark, off_top, off_dpre, slice_bytes;
   int bm_nq;              // wave bitmap: bitmap rows of 256 words
   int rk_nq, rk_shift;    // wave ranked bitmap: rows of 256 words and log2 block rows of the top level
+  int rk_short;           // symbolic: columns of so few entries are counted in a hash table
   int off_bm, off_pre, off_bvals, off_brows;
   // workgroup bitmap: largest range with one bit per row, bits of the top level, entries
   // (staged output entries) of a unit

@@ -926,6 +926,16 @@ hipError_t launch_bin(spkadd_plan_s* p, int b, bool numeric, KArgs& a_in, hipStr
   int acc = 0;
   if (layout_bin(p, b, numeric, a, acc)) {
     if (numeric && wave_ordered(p)) acc |= ACC_ORDERED;
+    // Table order is wanted and the columns are short: hash tables, whose cost grows with a
+    // column's entries, without their sort (150,000 columns, numeric pass in us, levels /
+    // tables: m = 2^21, u = 4 64.6 / 54.4, u = 10 67.5 / 62.6, u = 20 68.7 / 75; m = 2^28,
+    // u = 10 78.7 / 64, u = 32 80 / 85).  The average is that of all columns with entries.
+    const long long filled = (long long)p->n - p->bin_count[BIN_EMPTY];
+    if (numeric && acc == ACC_RANKED && b == BIN_W1 && a.unsorted && wave_pipe_ok(p->k, p->alpha_num_q, ACC_HASH) &&
+        3 * (long long)p->h_sum->nnz_in <= 2 * a.rk_short * filled) {
+      acc = ACC_HASH;
+      lds_layout_pipe(b, true, f64 ? 8 : 4, p->ts_num[b], acc, 0, p->k, a);
+    }
     return launch_wave_pipe(b, numeric, f64, acc, a, list, cnt, p->n_cu, s);
   }
   return launch_hash(b, numeric, f64, a, list, cnt, s);

@@ -510,6 +510,33 @@ __device__ __forceinline__ int bm_sym_unit(const KArgs& a, unsigned char* base, 
   return wave_total_add(newc);
 }
 
+// Entries of a column up to which the symbolic pass of the ranked bitmap counts in a hash
+// table instead (columns of at most 64 entries): the levels of a bitmap cost the same for
+// every column, probing and clearing a table of 64 or 128 slots grows with its entries.
+// 150,000 columns, plan and symbolic pass in us, levels / tables: m = 2^20, u = 4 104.8 /
+// 99.7, u = 20 105.3 / 116.6; m = 2^21, u = 10 119.9 / 104.6, u = 20 119.5 / 116.5, u = 32
+// 119.7 / 127.3; m = 2^24, u = 10 115.6 / 105.7, u = 20 114.9 / 116.9; m = 2^28, u = 20 129.8 /
+// 116.8, u = 32 130.0 / 127.2, u = 48 133.4 / 136.1.
+__host__ __device__ inline int rk_short(int shift, int nq) {
+  return shift == 6 ? (nq > 1 ? 5 * nq : 0) : 12 * (shift / 6 - 1) + 5 * nq;
+}
+constexpr int RK_SHORT_MOST = 24 + 5 * RK_TOP_ROWS;
+static_assert(2 * RK_SHORT_MOST <= 128, "a short column's table has at most 128 slots");
+
+// Symbolic: the distinct rows of a unit of at most RK_SHORT_MOST entries.
+__device__ __forceinline__ int short_sym_unit(const KArgs& a, unsigned char* base, int u, const int (&rows)[1]) {
+  const int lane = lane_id();
+  int* T = reinterpret_cast<int*>(base);
+  wave_sync();  // (the segment table read before shares the region)
+  T[lane] = -1;
+  T[64 + lane] = -1;
+  wave_sync();
+  const float none[1] = {0.f};
+  const int newc = insert_batch<1, false, float>(T, nullptr, u <= 32 ? 64 : 128, 0, u, rows, none, a.err);
+  wave_sync();
+  return wave_total_add(newc);
+}
+
 // Symbolic over the ranked bitmap (cleared for every unit).
 template <int E>
 __device__ __forceinline__ int rk_sym_unit(const KArgs& a, unsigned char* base, int u, const int (&rows)[E]) {
@@ -718,8 +745,15 @@ __device__ __forceinline__ void pipe_step(const KArgs& a, unsigned char* base, i
   } else if constexpr (NUM) {
     num_unit<E, V>(a, base, cur.u, cur.cnt, cur.o0, cur.rows, cur.vals);
   } else if constexpr (ACC != ACC_HASH) {
-    const int cnt = ACC == ACC_RANKED ? rk_sym_unit<E>(a, base, cur.u, cur.rows)
-                                      : bm_sym_unit<E>(a, base, cur.u, cur.rows);
+    int cnt;
+    if constexpr (ACC == ACC_BITMAP) {
+      cnt = bm_sym_unit<E>(a, base, cur.u, cur.rows);
+    } else if constexpr (E == 1) {
+      if (cur.u <= a.rk_short) cnt = short_sym_unit(a, base, cur.u, cur.rows);  // (uniform)
+      else cnt = rk_sym_unit<E>(a, base, cur.u, cur.rows);
+    } else {
+      cnt = rk_sym_unit<E>(a, base, cur.u, cur.rows);
+    }
     // one unconditional store instruction: every lane writes the count to its place (one
     // request; write-sink slots for the other lanes would be lines shared by the whole chip)
     gstore<int>((long long)(a.colcnt + cur.j), cnt);
@@ -796,9 +830,10 @@ __host__ __device__ inline void pipe_layout(int E, bool numeric, int vbytes, int
   const int adj_bytes = kc * 64 * (numeric ? 16 : 8);  // (rows, values) pointer pairs, or row pointers
   const int mark_bytes = (8 * E + 15) & ~15;
   a.ts_max = ts_max;
-  a.bm_nq = a.rk_nq = a.rk_shift = 0;
+  a.bm_nq = a.rk_nq = a.rk_shift = a.rk_short = 0;
   if (acc == ACC_RANKED) {
     rk_levels(rows, a.rk_shift, a.rk_nq);
+    a.rk_short = rk_short(a.rk_shift, a.rk_nq);
     const int low = rk_low_rows(E);
     a.off_bm = 0;
     a.off_pre = low * 1024;
