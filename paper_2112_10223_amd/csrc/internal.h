@@ -63,6 +63,7 @@ struct PlanParams {
   int g3_max;       // largest u_j of bin G3 (cap_in: none)
   int force_bin;    // -1 auto
   float win_fill;   // target window input count = cap_in * win_fill
+  int win_min;      // fewest windows of a window column
   int unsorted_in;  // input columns may be unsorted (validation checks only the row range)
 };
 

@@ -250,14 +250,17 @@ __global__ __launch_bounds__(PLAN_THREADS) void k_bin_scatter(PlanParams p, cons
   }
 }
 
-// Initial number of windows of each window column: P = ceil(u / (cap_in * fill)),
-// clamped to [1, m]; exclusive scan into wfirst[0..n_wcols].  One block.
+// Initial number of windows of each window column: P = ceil(u / (cap_in * fill)), at
+// least win_min where that makes no more than WIN_MIN_ALL windows, clamped to [1, m];
+// exclusive scan into wfirst[0..n_wcols].  One block.
+constexpr int WIN_MIN_ALL = 4096;
 __global__ __launch_bounds__(1024) void k_win_scan(PlanParams p, const int* __restrict__ list,
                                                    const int* __restrict__ binoff, const int* __restrict__ u,
                                                    int* __restrict__ wfirst, PlanSummary* __restrict__ sum) {
   __shared__ long long scratch[1024 / 64 + 1];
   const int* wcols = list + binoff[BIN_WIN];
   const int n_wcols = binoff[BIN_WIN + 1] - binoff[BIN_WIN];
+  const int win_min = max(1, min(p.win_min, WIN_MIN_ALL / max(n_wcols, 1)));
   const double target = (double)p.cap_in * (double)p.win_fill;
   long long carry = 0;
   for (int base = 0; base < n_wcols; base += 1024) {
@@ -266,7 +269,7 @@ __global__ __launch_bounds__(1024) void k_win_scan(PlanParams p, const int* __re
     if (c < n_wcols) {
       const int uj = u[wcols[c]];
       pc = (long long)ceil((double)uj / (target > 1.0 ? target : 1.0));
-      if (pc < 1) pc = 1;
+      if (pc < win_min) pc = win_min;
       if (pc > p.m) pc = p.m;
     }
     long long chunk = 0;

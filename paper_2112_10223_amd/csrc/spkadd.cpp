@@ -1050,6 +1050,13 @@ spkadd_status plan_build(spkadd_plan_s* p, int32_t m, int32_t n, int32_t k, cons
   p->pp.g3_max = o.window_cap || small_cap ? cap : f64 ? kG3MaxF64 : kG3MaxF32;
   p->pp.force_bin = o.force_bin;
   p->pp.win_fill = o.window_fill > 0 ? o.window_fill : kDefaultFill;
+  // The ordered pass gives a window one wavefront, which takes its entries one after another:
+  // where there are few windows, the columns of tall matrices get one per 2^17 rows at
+  // least (numeric pass with the fewest windows / with these, us: 10 inputs of 2^21 x 64,
+  // 6,000 entries a column 79 / 30, 1 of 2^24 x 11, 18,582 66 / 20; one per 2^18 rows also
+  // where there are many, 64 inputs of 2^24 x 512, 30,000 658 / 866).
+  p->pp.win_min = o.flags & SPKADD_FLAG_ORDERED ? (int)(((long long)m + (1 << 17) - 1) >> 17) : 1;
+  if (p->pp.win_min < 1) p->pp.win_min = 1;
   p->unsorted_in = (o.flags & SPKADD_FLAG_UNSORTED_IN) != 0;
   p->pp.unsorted_in = p->unsorted_in ? 1 : 0;
   for (int b = BIN_W1; b <= BIN_W16; ++b) {

@@ -90,3 +90,21 @@ def test_special_values_keep_their_bits(m, k, dtype):
             nan = np.isnan(want)
             assert np.array_equal(np.isnan(part), nan)
             assert np.array_equal(part[~nan].view(bits), want[~nan].view(bits))
+
+
+@pytest.mark.parametrize("m", [1 << 17, (1 << 17) + 1, 1 << 22, (1 << 31) - 2])
+@pytest.mark.parametrize("k,sizes", [(1, [20000]), (9, [6000, 40, 30000]), (40, [5000] * 70)])
+def test_row_windows_of_tall_matrices(m, k, sizes):
+    """Few long columns, which get more row windows than their entries ask for, and more columns:
+    bit-identical to the ordered oracle."""
+    import oracle
+    from paper_2112_10223_amd import binding
+    from tests.gpu_util import run_gpu
+    from tests.test_ranked_bitmap import tall_batch
+    note(f"ordered row windows m={m} k={k} columns={len(sizes)}")
+    b = tall_batch(m, k, sizes, np.float32 if k == 9 else np.float64, False, seed=m % 1000 + k)
+    got = run_gpu(b, binding.make_opts(flags=binding.SPKADD_FLAG_ORDERED), stats=True)
+    ref = oracle.spkadd_ordered(b)
+    assert got[3]["n_window_cols"] > 0
+    assert np.array_equal(got[0], ref.colptr) and np.array_equal(got[1], ref.rowidx)
+    assert np.array_equal(got[2], ref.val.astype(got[2].dtype))
