@@ -832,8 +832,11 @@ __host__ __device__ inline void pipe_layout(int E, bool numeric, int vbytes, int
   a.ts_max = ts_max;
   a.bm_nq = a.rk_nq = a.rk_shift = a.rk_short = 0;
   if (acc == ACC_RANKED) {
-    rk_levels(rows, a.rk_shift, a.rk_nq);
-    a.rk_short = rk_short(a.rk_shift, a.rk_nq);
+    int shift = 0, nq = 0;
+    rk_levels(rows, shift, nq);
+    a.rk_shift = (short)shift;
+    a.rk_nq = (short)nq;
+    a.rk_short = (short)rk_short(shift, nq);
     const int low = rk_low_rows(E);
     a.off_bm = 0;
     a.off_pre = low * 1024;
