@@ -68,9 +68,11 @@ typedef enum spkadd_dtype { SPKADD_F32 = 0, SPKADD_F64 = 1 } spkadd_dtype;
 #define SPKADD_FLAG_VALIDATE 1u /* check every input on the device in spkadd_plan */
 #define SPKADD_FLAG_TRACE 2u    /* time every kernel launch with HIP events */
 #define SPKADD_FLAG_TRACE_NUMERIC 4u /* time only the launches of spkadd_numeric */
-#define SPKADD_FLAG_UNSORTED_OUT 8u  /* the rows of each output column may come in any order: the hash
-                                        accumulators skip their sort (the paper's "if sorted output is
-                                        desired", Algorithm 5); bitmap accumulators are sorted anyway */
+#define SPKADD_FLAG_UNSORTED_OUT 8u  /* the rows of each output column may come in any order: columns
+                                        in hash tables skip their sort (the paper's "if sorted output is
+                                        desired", Algorithm 5).  Those are all columns with accum_mode 1,
+                                        short ones of very tall matrices and columns for one wavefront of
+                                        more than 128 inputs; the others come out sorted anyway */
 #define SPKADD_FLAG_UNSORTED_IN 16u  /* the rows of each input column may come in any order (hash
                                         accumulation needs none, Table I).  The row windows of long
                                         columns then count their entries by histogram and partition
@@ -83,8 +85,11 @@ typedef enum spkadd_dtype { SPKADD_F32 = 0, SPKADD_F64 = 1 } spkadd_dtype;
                                         (the order in which Algorithm 5 visits the inputs of a column,
                                         Section II-C): c = a_first, then c = c + a for each later term.
                                         Results are then reproducible bit for bit, whatever the launch.
+                                        For columns of more than 1024 entries, with hash tables, with more
+                                        than 128 inputs and with a load_factor_num of its own,
                                         spkadd_numeric runs one more pass that re-reads the inputs and
-                                        rewrites the values.  The output is sorted (UNSORTED_OUT is
+                                        rewrites the values.  A row outside the matrix makes the pass's
+                                        result invalid and spkadd_get_stats report it.  The output is sorted (UNSORTED_OUT is
                                         ignored).  With SPKADD_FLAG_UNSORTED_IN, spkadd_plan returns
                                         SPKADD_ERR_UNSUPPORTED; so it does when k is so large that the
                                         pass's per-unit table of the k inputs does not fit on chip
@@ -93,7 +98,7 @@ typedef enum spkadd_dtype { SPKADD_F32 = 0, SPKADD_F64 = 1 } spkadd_dtype;
 /* opts.force_bin: test hook that routes columns to one accumulator family */
 #define SPKADD_BIN_AUTO (-1)
 #define SPKADD_BIN_WAVE 0   /* one wavefront per column (columns with u_j <= 1024) */
-#define SPKADD_BIN_WG 1     /* one workgroup per column (columns with u_j <= window_cap) */
+#define SPKADD_BIN_WG 1     /* one workgroup per column (columns up to the limit given at window_cap) */
 #define SPKADD_BIN_WINDOW 2 /* sliding-hash row windows for every non-empty column */
 
 /* opts.accum_mode */
@@ -105,8 +110,11 @@ typedef enum spkadd_dtype { SPKADD_F32 = 0, SPKADD_F64 = 1 } spkadd_dtype;
 typedef struct spkadd_opts {
   uint32_t flags;        /* SPKADD_FLAG_* */
   int32_t force_bin;     /* SPKADD_BIN_*; 0 is "wave", so use SPKADD_BIN_AUTO (-1) for auto */
-  int32_t window_cap;    /* max input entries per row window and per workgroup column;
-                            0 = auto.  Small values force the sliding hash on small inputs. */
+  int32_t window_cap;    /* max input entries per row window and, unless 0, per column of one
+                            workgroup.  0 = auto: 4096 (fp64 3072) per window and 8192 (6144) per
+                            column; with SPKADD_FLAG_ORDERED, with hash tables and below 64 columns
+                            3072 (2048) for both.  Small values force the sliding hash on small
+                            inputs. */
   int32_t hash_mode;     /* 0 = multiplicative hash; 1 = degenerate hash (every row starts
                             probing at slot 0), a test hook for long probe chains */
   int32_t wave_max;      /* largest u_j handled one wavefront per column (64..1024); 0 = auto */
@@ -168,7 +176,10 @@ void spkadd_opts_default(spkadd_opts* opts);
  * per column and input (k rounded up to a multiple of 4), at most 1 GiB.  A sum that
  * runs out of device memory gives that copy up before it reports OOM.  Every array is
  * rounded up to a power of two of at least 4 KiB.
- * Errors: INVALID (null pointers, k < 1, negative sizes, bad option values, or
+ * Errors: UNSUPPORTED (tables of k inputs that do not fit on chip: above 660 to 1,840
+ * inputs where a column goes to one wavefront, by its entries, 3,700 to 7,300 where all
+ * go to workgroups or row windows, less with small load factors), here when the plan waits, else from
+ * spkadd_symbolic; INVALID (null pointers, k < 1, negative sizes, bad option values, or
  * malformed inputs when SPKADD_FLAG_VALIDATE is set), OOM, HIP; OVERFLOW (some u_j
  * above INT32_MAX) here when the plan waits, else from spkadd_symbolic.
  */
@@ -186,8 +197,8 @@ spkadd_status spkadd_plan(spkadd_plan_t* out, int32_t m, int32_t n, int32_t k, c
  *              the plan's stream differs, the first call orders itself after the
  *              plan's device work.
  * Errors: INVALID (null arguments), OVERFLOW (nnz(B) > INT32_MAX, or some u_j above
- * INT32_MAX when spkadd_plan did not wait), UNSUPPORTED (row windows that need more
- * LDS than the device has, when spkadd_plan did not wait), HIP.
+ * INT32_MAX when spkadd_plan did not wait), UNSUPPORTED (tables that need more LDS than
+ * the device has, when spkadd_plan did not wait), OOM, HIP.
  * It may be called again; every call recomputes the counts.
  */
 spkadd_status spkadd_symbolic(spkadd_plan_t plan, int32_t* colptr_c, int64_t* nnz_c, hipStream_t stream);
@@ -263,7 +274,8 @@ typedef struct spkadd_stats {
   int32_t n_window_cols; /* columns split into row windows (sliding hash) */
   int32_t n_windows;     /* row windows over all window columns */
   int32_t window_levels; /* refinement rounds the window split needed */
-  int32_t window_cap;    /* input entries per window target used */
+  int32_t window_cap;    /* input entries per row window used (columns of one workgroup may hold
+                            more, see spkadd_opts) */
   int32_t wave_max;      /* wave bin limit used */
 } spkadd_stats;
 spkadd_status spkadd_get_stats(spkadd_plan_t plan, spkadd_stats* out);

@@ -4,8 +4,9 @@
 // into the slot of its row, so each output value is the sequential sum of its terms
 // in input order.  The numeric kernels add in the order their atomics happen to
 // meet, which is bounded by the summation error bound but not reproducible bit for
-// bit.  This pass runs after the numeric pass has written the sorted rows of B and
-// sums every output entry again in input order, one rounding per addition in the
+// bit.  (The pipelined wave kernels on bitmaps can add in input order themselves,
+// wave_device.h.)  This pass runs after the numeric pass has written the sorted rows of B
+// and sums every output entry of the other columns and windows again in input order, one rounding per addition in the
 // values' own type: the first term is stored, each later term added.
 //
 // One wavefront per unit (a column, or a row window of a window column).  The unit's

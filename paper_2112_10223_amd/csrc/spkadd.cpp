@@ -448,8 +448,13 @@ void clear_trace(spkadd_plan_s* p) {
 // share it at.  The ordered pass keeps the smaller ones, which its tables are sized by.
 constexpr int kDefaultCapF32 = 4096, kDefaultCapF64 = 3072;
 constexpr int kHashCapF32 = 3072, kHashCapF64 = 2048;
-// Sums of fewer columns than this keep the smaller capacities too: one workgroup per
-// column would leave most CUs idle, the row windows of a column are shared out.
+// Sums of fewer columns than this keep the smaller capacities too, and the row windows of
+// columns above them: their accumulation is shared out over more workgroups.  That gains
+// the numeric pass of a kept plan about 1 us where 64 long columns are all there is (64
+// columns of 6,000 entries 11.7 us in windows, 12.7 in one workgroup each; at 256 columns
+// the latter are level), and costs a whole sum the windows' planning: 63 / 64 columns of
+// 4,500 entries 250 / 92 us, 16 long ones among 64 226 / 93, 512 251 / 91.  A lower line
+// has not been taken: the fewest columns it would pay at are not measured.
 constexpr int kManyCols = 64;
 // Longest column of one workgroup of 1024 threads (two share a CU's LDS).
 constexpr int kG3MaxF32 = 8192, kG3MaxF64 = 6144;

@@ -14,8 +14,9 @@ struct WaveBinTable {
   int ts[NWAVE_BINS];
 };
 
-// Wavefronts per SIMD of the fused launch: its registers are held to that (its longest
-// columns would take 137 and leave three).
+// Wavefronts per SIMD of the fused launch: its registers are held to that.  Its longest
+// columns would take 136 (145 with two inputs per lane) and leave three; held to 128 it
+// spills 4 (15), in the bodies of the bins E = 16 alone.
 constexpr int SYM_FUSED_WAVES = 4;
 
 // Counts the distinct rows of every column of the wave bins.  The bins' column

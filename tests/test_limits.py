@@ -19,7 +19,7 @@ MOST = {np.float32: 4767, np.float64: 4373}
 def test_many_inputs_in_workgroup_columns(dtype, less):
     """Columns of one workgroup (all three sizes) and row windows of thousands of inputs, most of
     them empty in a column; a few inputs more are refused.  (Short columns are sent to workgroups
-    too: the four wavefronts of a workgroup hold tables for about 1,900 inputs.)"""
+    too: wavefronts hold tables for 660 to 1,840 inputs.)"""
     from paper_2112_10223_amd import binding
     opts = binding.make_opts(force_bin=binding.SPKADD_BIN_WG)
     k = MOST[dtype] - less
