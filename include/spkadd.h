@@ -178,8 +178,8 @@ void spkadd_opts_default(spkadd_opts* opts);
  * rounded up to a power of two of at least 4 KiB.
  * Errors: UNSUPPORTED (tables of k inputs that do not fit on chip: above 660 to 1,840
  * inputs where a column goes to one wavefront, by its entries, 3,700 to 7,300 where all
- * go to workgroups or row windows, less with small load factors), here when the plan waits, else from
- * spkadd_symbolic; INVALID (null pointers, k < 1, negative sizes, bad option values, or
+ * go to workgroups or row windows, less with small load factors), here when the plan
+ * waits, else from spkadd_symbolic; INVALID (null pointers, k < 1, negative sizes, bad option values, or
  * malformed inputs when SPKADD_FLAG_VALIDATE is set), OOM, HIP; OVERFLOW (some u_j
  * above INT32_MAX) here when the plan waits, else from spkadd_symbolic.
  */
