@@ -1060,7 +1060,9 @@ spkadd_status plan_build(spkadd_plan_s* p, int32_t m, int32_t n, int32_t k, cons
   // least (numeric pass with the fewest windows / with these, us: 10 inputs of 2^21 x 64,
   // 6,000 entries a column 79 / 30, 1 of 2^24 x 11, 18,582 66 / 20; one per 2^18 rows also
   // where there are many, 64 inputs of 2^24 x 512, 30,000 658 / 866).
-  p->pp.win_min = o.flags & SPKADD_FLAG_ORDERED ? (int)(((long long)m + (1 << 17) - 1) >> 17) : 1;
+  // (Half as many in the fixed region, where the windows' arrays count.)
+  const int win_rows = p->region_mode ? 18 : 17;
+  p->pp.win_min = o.flags & SPKADD_FLAG_ORDERED ? (int)(((long long)m + (1 << win_rows) - 1) >> win_rows) : 1;
   if (p->pp.win_min < 1) p->pp.win_min = 1;
   p->unsorted_in = (o.flags & SPKADD_FLAG_UNSORTED_IN) != 0;
   p->pp.unsorted_in = p->unsorted_in ? 1 : 0;
