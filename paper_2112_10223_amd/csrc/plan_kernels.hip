@@ -4,6 +4,7 @@
 
 #include "device.h"
 #include "internal.h"
+#include "launch_grid.h"
 #include "scan_device.h"
 
 namespace spk {
@@ -316,8 +317,8 @@ __global__ __launch_bounds__(256) void k_win_fill(PlanParams p, const int* const
                                                   int* __restrict__ wlin) {
   __shared__ int wl[256 / 64], wi[256 / 64];
   __shared__ int carry_s;
-  const int c = blockIdx.x;
-  if (c >= n_wcols) return;
+  if (block_number() >= n_wcols) return;
+  const int c = (int)block_number();
   const int w0 = wfirst[c], P = wfirst[c + 1] - w0;
   const int j = wcols[c];
   const int lane = lane_id(), w = threadIdx.x >> 6;
@@ -572,7 +573,7 @@ __device__ __forceinline__ void locate_chunk(const PlanParams& p, const int* con
 
 __global__ __launch_bounds__(WLOC_THREADS) void k_win_locate(PlanParams p, const int* const* __restrict__ cp,
                                                              const int* const* __restrict__ ri,
-                                                             const int* __restrict__ wcols,
+                                                             int n_chunks, const int* __restrict__ wcols,
                                                              const int* __restrict__ wfirst,
                                                              const int* __restrict__ brow,
                                                              const int* __restrict__ chfirst,
@@ -588,7 +589,8 @@ __global__ __launch_bounds__(WLOC_THREADS) void k_win_locate(PlanParams p, const
   __shared__ int sb[WLOC_LDS];  // the column's boundary rows
   __shared__ int red[WLOC_THREADS / 64 + 1];
   const int tid = threadIdx.x;
-  const int c = chcol[blockIdx.x], chunk = blockIdx.x - chfirst[c];
+  if (block_number() >= n_chunks) return;
+  const int blk = (int)block_number(), c = chcol[blk], chunk = blk - chfirst[c];
   const int j = wcols[c];
   const int first = wfirst[c] + c;
   const int P = wfirst[c + 1] - wfirst[c];  // windows; boundaries first .. first + P
@@ -629,7 +631,7 @@ __global__ __launch_bounds__(WLOC_THREADS) void k_win_locate(PlanParams p, const
 __global__ __launch_bounds__(256) void k_win_bpos_t(long long total, int k, const int* __restrict__ bcol,
                                                     const int* __restrict__ wfirst, const int* __restrict__ wlin,
                                                     const int* __restrict__ bpos_t, int* __restrict__ bpos) {
-  const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
+  const long long t = block_number() * 256 + threadIdx.x;
   if (t >= total) return;
   const int b = (int)(t / k), i = (int)(t - (long long)b * k);
   const int c = bcol[b];
@@ -657,11 +659,12 @@ __global__ __launch_bounds__(WSL_THREADS) void k_win_search_lin(PlanParams p, co
                                                                 const int* const* __restrict__ ri,
                                                                 const int* __restrict__ wcols,
                                                                 const int* __restrict__ wfirst,
-                                                                const int* __restrict__ wlin,
+                                                                const int* __restrict__ wlin, int n_wcols,
                                                                 int* __restrict__ bpos) {
   const int groups = (p.k + WSL_GROUP - 1) / WSL_GROUP;
-  const int blk = xcd_remap(blockIdx.x, gridDim.x);
-  const int c = blk / groups, g = blk - c * groups;
+  const long long blk = (long long)blockIdx.y * gridDim.x + xcd_remap(blockIdx.x, gridDim.x);
+  if (blk >= (long long)n_wcols * groups) return;
+  const int c = (int)((unsigned)blk / (unsigned)groups), g = (int)blk - c * groups;
   if (!wlin[c]) return;  // k_win_locate's column
   const int j = wcols[c];
   const int first = wfirst[c] + c;
@@ -843,7 +846,7 @@ __global__ __launch_bounds__(256) void k_win_refine_search(PlanParams p, const i
                                                            const int* __restrict__ q,
                                                            const int* __restrict__ bpos_old,
                                                            int* __restrict__ bpos_new) {
-  const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
+  const long long t = block_number() * 256 + threadIdx.x;
   if (t >= (long long)n_bounds_new * p.k) return;
   const int nb = (int)(t / p.k), i = (int)(t - (long long)nb * p.k);
   const int w = bpar[nb], piece = bpiece[nb], c = bcol_new[nb];
@@ -875,8 +878,8 @@ __global__ __launch_bounds__(256) void k_win_colsum(int n_wcols, const int* __re
                                                     const int* __restrict__ win_cnt, int* __restrict__ colcnt,
                                                     int* __restrict__ win_off) {
   __shared__ int scratch[256 / 64 + 1];
-  const int c = blockIdx.x;
-  if (c >= n_wcols) return;
+  if (block_number() >= n_wcols) return;
+  const int c = (int)block_number();
   const int w0 = wfirst[c], w1 = wfirst[c + 1];
   int carry = 0;
   for (int base = w0; base < w1; base += 256) {
@@ -1055,7 +1058,7 @@ void launch_win_fill(const PlanParams& p, const int* const* d_cp, const int* con
                      const int* d_u, int n_wcols, const int* d_wfirst, int* d_win_c, int* d_brow, int* d_bcol,
                      int* d_wlin, hipStream_t s) {
   if (n_wcols == 0) return;
-  k_win_fill<<<n_wcols, 256, 0, s>>>(p, d_cp, d_ri, d_wcols, d_u, n_wcols, d_wfirst, d_win_c, d_brow, d_bcol,
+  k_win_fill<<<grid_rows(n_wcols, 256), 256, 0, s>>>(p, d_cp, d_ri, d_wcols, d_u, n_wcols, d_wfirst, d_win_c, d_brow, d_bcol,
                                      d_wlin);
 }
 
@@ -1065,15 +1068,15 @@ void launch_win_search(const PlanParams& p, const int* const* d_cp, const int* c
                        int* d_bpos, hipStream_t s) {
   if (n_wcols <= 0 || p.k == 0) return;
   const long long groups = (p.k + WSL_GROUP - 1) / WSL_GROUP;
-  k_win_search_lin<<<(unsigned)(n_wcols * groups), WSL_THREADS, 0, s>>>(p, d_cp, d_ri, d_wcols, d_wfirst, d_wlin,
-                                                                         d_bpos);
+  k_win_search_lin<<<grid_rows(n_wcols * groups, WSL_THREADS), WSL_THREADS, 0, s>>>(p, d_cp, d_ri, d_wcols, d_wfirst,
+                                                                                    d_wlin, n_wcols, d_bpos);
   if (n_chunks <= 0) return;
   const int kt = p.k <= WIN_LDS_K ? p.k : 0;
   const size_t lds = (size_t)8 * kt + 4 * (2 * (size_t)kt + 1);
-  k_win_locate<<<(unsigned)n_chunks, WLOC_THREADS, lds, s>>>(p, d_cp, d_ri, d_wcols, d_wfirst, d_brow, d_chfirst,
-                                                            d_chcol, d_bpos_t);
+  k_win_locate<<<grid_rows(n_chunks, WLOC_THREADS), WLOC_THREADS, lds, s>>>(p, d_cp, d_ri, n_chunks, d_wcols, d_wfirst,
+                                                                            d_brow, d_chfirst, d_chcol, d_bpos_t);
   const long long total = (long long)n_bounds * p.k;
-  k_win_bpos_t<<<grid_for(total, 256), 256, 0, s>>>(total, p.k, d_bcol, d_wfirst, d_wlin, d_bpos_t, d_bpos);
+  k_win_bpos_t<<<grid_rows((total + 255) / 256, 256), 256, 0, s>>>(total, p.k, d_bcol, d_wfirst, d_wlin, d_bpos_t, d_bpos);
 }
 
 void launch_win_count(const PlanParams& p, int n_windows, const int* d_win_c, const int* d_brow, const int* d_bpos,
@@ -1100,8 +1103,8 @@ void launch_win_refine_search(const PlanParams& p, const int* const* d_ri, int n
                               const int* d_bpos_old, int* d_bpos_new, hipStream_t s) {
   const long long work = (long long)n_bounds_new * p.k;
   if (work == 0) return;
-  k_win_refine_search<<<grid_for(work, 256), 256, 0, s>>>(p, d_ri, n_bounds_new, d_bcol_new, d_brow_new, d_bpar,
-                                                          d_bpiece, d_q, d_bpos_old, d_bpos_new);
+  k_win_refine_search<<<grid_rows((work + 255) / 256, 256), 256, 0, s>>>(
+      p, d_ri, n_bounds_new, d_bcol_new, d_brow_new, d_bpar, d_bpiece, d_q, d_bpos_old, d_bpos_new);
 }
 
 void launch_win_records(int n_windows, const int* d_wcols, const int* d_win_c, const int* d_brow, int4* d_wrec,
@@ -1113,7 +1116,7 @@ void launch_win_records(int n_windows, const int* d_wcols, const int* d_win_c, c
 void launch_win_colsum(int n_wcols, const int* d_wcols, const int* d_wfirst, const int* d_win_cnt, int* d_colcnt,
                        int* d_win_off, hipStream_t s) {
   if (n_wcols == 0) return;
-  k_win_colsum<<<n_wcols, 256, 0, s>>>(n_wcols, d_wcols, d_wfirst, d_win_cnt, d_colcnt, d_win_off);
+  k_win_colsum<<<grid_rows(n_wcols, 256), 256, 0, s>>>(n_wcols, d_wcols, d_wfirst, d_win_cnt, d_colcnt, d_win_off);
 }
 
 size_t scan_tmp_bytes(int64_t len) {

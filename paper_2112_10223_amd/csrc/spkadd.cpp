@@ -17,6 +17,7 @@
 #include <vector>
 
 #include "internal.h"
+#include "launch_grid.h"
 #include "ordered.h"
 #include "region.h"
 #include "wave_fused.h"
@@ -910,6 +911,26 @@ bool wave_ordered(const spkadd_plan_s* p) {
   return true;
 }
 
+// Launches one(args, list, units) over a bin's units of `threads` threads each: in one launch
+// as long as they fit a grid row (not so 2^32 / 512 row windows), else in several.  Windows
+// (no list) are numbered from the launch's first one.
+template <typename F>
+hipError_t launch_units(KArgs a, const int* list, int units, int threads, F one) {
+  const int most = (int)grid_row(threads) & ~1023;  // (whole workgroups of several units)
+  for (; units > most; units -= most) {
+    const hipError_t e = one(a, list, most);
+    if (e != hipSuccess) return e;
+    if (list) {
+      list += most;
+    } else {
+      a.wrec += most;
+      a.win_cnt += most;
+      a.win_off += most;
+    }
+  }
+  return one(a, list, units);
+}
+
 // Launches the symbolic or numeric kernel of bin b.
 hipError_t launch_bin(spkadd_plan_s* p, int b, bool numeric, KArgs& a_in, hipStream_t s) {
   const int cnt = b == BIN_WIN ? p->n_windows : p->bin_count[b];
@@ -926,7 +947,9 @@ hipError_t launch_bin(spkadd_plan_s* p, int b, bool numeric, KArgs& a_in, hipStr
   const int* list = b == BIN_WIN ? nullptr : p->d_list + p->binoff[b];
   if (wg_bitmap_bin(p, b)) {
     wg_bitmap_layout(p, b, numeric, a);
-    return launch_bitmap_wg(b, numeric, f64, a, list, cnt, s);
+    return launch_units(a, list, cnt, bitmap_wg_threads(b, a.wg_cap), [&](const KArgs& x, const int* l, int n) {
+      return launch_bitmap_wg(b, numeric, f64, x, l, n, s);
+    });
   }
   int acc = 0;
   if (layout_bin(p, b, numeric, a, acc)) {
@@ -943,7 +966,9 @@ hipError_t launch_bin(spkadd_plan_s* p, int b, bool numeric, KArgs& a_in, hipStr
     }
     return launch_wave_pipe(b, numeric, f64, acc, a, list, cnt, p->n_cu, s);
   }
-  return launch_hash(b, numeric, f64, a, list, cnt, s);
+  return launch_units(a, list, cnt, bin_threads(b) / bin_units_per_block(b), [&](const KArgs& x, const int* l, int n) {
+    return launch_hash(b, numeric, f64, x, l, n, s);
+  });
 }
 
 // The fused symbolic launch of the wave bins (wave_fused.hip): each bin's accumulator

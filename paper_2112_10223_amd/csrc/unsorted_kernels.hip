@@ -8,6 +8,7 @@
 // numeric pass gathers.  The window kernels then read a single input, the buckets.
 #include "device.h"
 #include "internal.h"
+#include "launch_grid.h"
 
 namespace spk {
 
@@ -46,8 +47,8 @@ __global__ __launch_bounds__(256) void k_uwin_nch(PlanParams p, int n_wcols, con
 
 __global__ __launch_bounds__(256) void k_uwin_chfill(int n_wcols, const int* __restrict__ chfirst,
                                                      int* __restrict__ chcol) {
-  const int c = blockIdx.x;
-  if (c >= n_wcols) return;
+  if (block_number() >= n_wcols) return;
+  const int c = (int)block_number();
   for (int t = chfirst[c] + threadIdx.x; t < chfirst[c + 1]; t += 256) chcol[t] = c;
 }
 
@@ -58,7 +59,7 @@ __global__ __launch_bounds__(256) void k_uwin_chfill(int n_wcols, const int* __r
 // when the column has at most UW_LDS_WIN of them, else by global atomics per entry.
 template <bool SCATTER>
 __global__ __launch_bounds__(UW_THREADS) void k_uwin_pass(PlanParams p, const int* const* __restrict__ cp,
-                                                        const int* const* __restrict__ ri,
+                                                        const int* const* __restrict__ ri, int n_chunks,
                                                         const int* __restrict__ wcols, const int* __restrict__ wfirst,
                                                         const int* __restrict__ brow,
                                                         const int* __restrict__ chfirst,
@@ -71,7 +72,8 @@ __global__ __launch_bounds__(UW_THREADS) void k_uwin_pass(PlanParams p, const in
   __shared__ int lbro[UW_LDS_WIN + 1];
   __shared__ int red[UW_THREADS / 64 + 1];
   const int tid = threadIdx.x;
-  const int c = chcol[blockIdx.x], chunk = blockIdx.x - chfirst[c];
+  if (block_number() >= n_chunks) return;
+  const int blk = (int)block_number(), c = chcol[blk], chunk = blk - chfirst[c];
   const int j = wcols[c], w0 = wfirst[c], P = wfirst[c + 1] - w0;
   const int* bro = brow + w0 + c;
   const bool lds_win = P <= UW_LDS_WIN;
@@ -215,23 +217,23 @@ void launch_uwin_chunks(const PlanParams& p, int n_wcols, const int* d_wcols, co
 
 void launch_uwin_chfill(int n_wcols, const int* d_chfirst, int* d_chcol, hipStream_t s) {
   if (n_wcols <= 0) return;
-  k_uwin_chfill<<<n_wcols, 256, 0, s>>>(n_wcols, d_chfirst, d_chcol);
+  k_uwin_chfill<<<grid_rows(n_wcols, 256), 256, 0, s>>>(n_wcols, d_chfirst, d_chcol);
 }
 
 void launch_uwin_hist(const PlanParams& p, const int* const* d_cp, const int* const* d_ri, int n_chunks,
                       const int* d_wcols, const int* d_wfirst, const int* d_brow, const int* d_chfirst,
                       const int* d_chcol, int* d_cnt, hipStream_t s) {
   if (n_chunks <= 0) return;
-  k_uwin_pass<false><<<n_chunks, UW_THREADS, 0, s>>>(p, d_cp, d_ri, d_wcols, d_wfirst, d_brow, d_chfirst, d_chcol,
-                                                     d_cnt, nullptr, nullptr, nullptr);
+  k_uwin_pass<false><<<grid_rows(n_chunks, UW_THREADS), UW_THREADS, 0, s>>>(
+      p, d_cp, d_ri, n_chunks, d_wcols, d_wfirst, d_brow, d_chfirst, d_chcol, d_cnt, nullptr, nullptr, nullptr);
 }
 
 void launch_uwin_scatter(const PlanParams& p, const int* const* d_cp, const int* const* d_ri, int n_chunks,
                          const int* d_wcols, const int* d_wfirst, const int* d_brow, const int* d_chfirst,
                          const int* d_chcol, int* d_gcur, int* d_brows, long long* d_bsrc, hipStream_t s) {
   if (n_chunks <= 0) return;
-  k_uwin_pass<true><<<n_chunks, UW_THREADS, 0, s>>>(p, d_cp, d_ri, d_wcols, d_wfirst, d_brow, d_chfirst, d_chcol,
-                                                    nullptr, d_gcur, d_brows, d_bsrc);
+  k_uwin_pass<true><<<grid_rows(n_chunks, UW_THREADS), UW_THREADS, 0, s>>>(
+      p, d_cp, d_ri, n_chunks, d_wcols, d_wfirst, d_brow, d_chfirst, d_chcol, nullptr, d_gcur, d_brows, d_bsrc);
 }
 
 void launch_uwin_bpos(int n_windows, const int* d_win_c, const int* d_wfirst, const int* d_boff, int* d_bpos,

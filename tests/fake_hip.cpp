@@ -36,6 +36,7 @@ std::vector<std::string> g_log;
 int g_fail_records = 0;
 long g_events = 0, g_events_made = 0, g_foreign_records = 0;
 int g_tables = 0, g_stale_tables = 0;  // launches with a copy of the column pointers; with a freed one
+std::map<std::string, size_t> g_units;  // blocks launched of each kernel
 struct { dim3 g, b; size_t lds; hipStream_t s; } g_call;
 
 hipError_t ret(hipError_t e) {
@@ -71,6 +72,12 @@ int fake_last_error() { return (int)g_last; }
 int fake_log_size() { return (int)g_log.size(); }
 const char* fake_log(int i) { return g_log[(size_t)i].c_str(); }
 void fake_log_clear() { g_log.clear(); }
+// blocks launched of the kernels whose names hold `part`
+size_t fake_blocks(const char* part) {
+  size_t n = 0;
+  for (auto& x : g_units) n += x.first.find(part) != std::string::npos ? x.second : 0;
+  return n;
+}
 int fake_bin_g1() { return spk::BIN_G1; }
 int fake_bin_g3() { return spk::BIN_G3; }
 int fake_bin_win() { return spk::BIN_WIN; }
@@ -93,9 +100,16 @@ hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* lds, hipStream_t*
   *s = g_call.s;
   return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t lds, hipStream_t s) {
+hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t lds, hipStream_t s) {
   using spk::PlanSummary;
   const std::string& name = g_kernels[f];
+  // fewer than 2^32 work-items along each dimension of a grid
+  if (((size_t)g.x * b.x) >> 32 || ((size_t)g.y * b.y) >> 32) {
+    note("refused", s, f);
+    g_log.push_back(name);
+    return ret(hipErrorInvalidConfiguration);
+  }
+  g_units[name] += (size_t)g.x * g.y;
   auto is = [&](const char* k) { return name.find(k) != std::string::npos; };
   size_t fixed = 0;  // the kernel's own LDS arrays
   for (const char* k : {"k_bitmap_wgILi", "k_hash_wgILi"})

@@ -14,7 +14,7 @@ import ctypes, json, sys
 sys.path.insert(0, {root!r})
 F = ctypes.CDLL({fake!r}, mode=ctypes.RTLD_GLOBAL)
 F.fake_limit.argtypes = [ctypes.c_size_t]
-for f in ("fake_used", "fake_peak"):
+for f in ("fake_used", "fake_peak", "fake_blocks"):
     getattr(F, f).restype = ctypes.c_size_t
 F.fake_log.restype = ctypes.c_char_p
 from paper_2112_10223_amd import binding as B

@@ -25,6 +25,61 @@ def test_the_stand_in_runs_every_path(run):
         assert any(k in x for x in out[2]), k
 
 
+# ---- launches ----
+
+ROW = {threads: (2**32 - 1) // threads for threads in (64, 256, 512, 1024)}
+
+
+@pytest.mark.parametrize("what, opts, bins, windows, kernel, blocks", [
+    # row windows, of which a workgroup takes one
+    ("windows", dict(), {"WIN": 2}, ROW[512] + 1, "k_bitmap_wg", 2 * (ROW[512] + 1)),
+    ("windows", dict(window_cap=8192), {"WIN": 2}, ROW[1024] + 1, "k_bitmap_wg", 2 * (ROW[1024] + 1)),
+    ("windows", dict(accum_mode=1), {"WIN": 2}, 2 * ROW[512] + 1, "k_hash_wg", 2 * (2 * ROW[512] + 1)),
+    # workgroup columns
+    ("columns", dict(), {"G1": ROW[256] + 1}, 0, "k_bitmap_wg", 2 * (ROW[256] + 1)),
+    ("columns", dict(), {"G3": ROW[1024] + 1}, 0, "k_bitmap_wg", 2 * (ROW[1024] + 1)),
+    ("columns", dict(accum_mode=1), {"G1": ROW[256] + 1}, 0, "k_hash_wg", 2 * (ROW[256] + 1)),
+    # columns cut into windows, of which the planning kernels take one a workgroup
+    ("columns", dict(), {"WIN": ROW[256] + 1}, ROW[256] + 1, "k_win_fill", ROW[256] + 1),
+    ("columns", dict(flags=16), {"WIN": ROW[256] + 1}, ROW[256] + 1, "k_uwin_chfill", ROW[256] + 1),
+    # a wavefront a column, four of them a workgroup
+    ("waves", dict(accum_mode=1), {"W3": ROW[64] + 1}, 0, "k_num_wave", (ROW[64] + 4) // 4),
+])
+def test_launches_of_more_blocks_than_a_grid_row(run, what, opts, bins, windows, kernel, blocks):
+    """As many units as make 2^32 work-items and more of a launch: every launch stays below that,
+    and together they have a block for every unit."""
+    n = sum(bins.values())
+    out = run(f"""
+        F.fake_limit(1 << 40)
+        W3 = 3
+        for b, c in {bins!r}.items():
+            BINS[dict(W3=3, G1=G1, G3=G3, WIN=WIN)[b]] = c
+        WINDOWS.value, TOTAL.value = {windows}, 40
+        st = Sum(1 << 30, {n}, {65 if what == "waves" else 2}, **{opts!r}).all(stream(0))
+        out = [st, [x[0] for x in log() if x[0] == "refused"], F.fake_blocks({kernel!r}.encode())]
+    """)
+    assert out[0] == [0, 0, 0] and out[1] == []
+    assert blocks <= out[2] <= blocks + 2 * 4096 * 3, out[2] - blocks
+
+
+@pytest.mark.parametrize("unsorted", [False, True])
+def test_passes_over_more_elements_than_a_grid_row(run, unsorted):
+    """More chunks of the window columns' entries than a grid row has blocks, and (sorted inputs)
+    2^32 boundary positions and more."""
+    out = run(f"""
+        F.fake_limit(1 << 40)
+        BINS[WIN], WINDOWS.value, TOTAL.value = 2, {1 << 20 if unsorted else 1 << 25}, {ROW[256] + 1}
+        st = Sum(1 << 30, 2, {2 if unsorted else 128}, flags={16 if unsorted else 0}).all(stream(0))
+        out = [st, [x[0] for x in log() if x[0] == "refused"], F.fake_blocks(b"k_uwin_pass"),
+               F.fake_blocks(b"k_win_locate"), F.fake_blocks(b"k_win_bpos_t")]
+    """)
+    assert out[0] == [0, 0, 0] and out[1] == []
+    if unsorted:
+        assert out[2] >= 2 * (ROW[256] + 1)
+    else:
+        assert out[3] >= ROW[256] + 1 and out[4] * 256 >= ((1 << 25) + 2) * 128
+
+
 # ---- events ----
 
 def test_events_stay_on_their_device(run):
