@@ -17,6 +17,7 @@
 #include <climits>
 
 #include "batch_device.h"
+#include "launch_grid.h"
 #include "scan_device.h"
 
 namespace spk {
@@ -240,8 +241,8 @@ __global__ __launch_bounds__(64 * PIPE_WAVES_PER_BLOCK) void k_batch_wave(BatchA
 __global__ __launch_bounds__(BATCH_SCAN_THREADS) void k_batch_scan(BatchArgs b) {
   __shared__ long long scratch[BATCH_SCAN_THREADS / 64 + 1];
   __shared__ int buf[BATCH_SCAN_THREADS * 16];
-  const int r = blockIdx.x;
-  if (r >= b.hdr->nreq) return;
+  if (block_number() >= b.hdr->nreq) return;
+  const int r = (int)block_number();
   const BatchReq& q = b.reqs[r];
   if (b.status[r] & REQ_TOO_LARGE) {  // counts are incomplete: write nothing
     if (threadIdx.x == 0) b.nnz[r] = -1;
@@ -265,7 +266,7 @@ void launch_batch_plan(const BatchArgs& b, hipStream_t s) {
 }
 
 void launch_batch_scan(const BatchArgs& b, hipStream_t s) {
-  k_batch_scan<<<b.max_reqs, BATCH_SCAN_THREADS, 0, s>>>(b);
+  k_batch_scan<<<grid_rows(b.max_reqs, BATCH_SCAN_THREADS), BATCH_SCAN_THREADS, 0, s>>>(b);
 }
 
 template <bool NUM, typename V, int ACC>

@@ -80,6 +80,21 @@ def test_passes_over_more_elements_than_a_grid_row(run, unsorted):
         assert out[3] >= ROW[256] + 1 and out[4] * 256 >= ((1 << 25) + 2) * 128
 
 
+@pytest.mark.parametrize("most", [1000, 2**22])
+def test_a_batch_for_many_requests(run, most):
+    """A batch made for more requests than a grid row has blocks of its colptr pass."""
+    out = run(f"""
+        h, ptrs = ctypes.c_void_p(), (ctypes.c_void_p * 2)(ADDR, ADDR)
+        a = ctypes.addressof(ptrs)
+        q = B.Request(100, 5, 2, a, a, a, ADDR, ADDR, ADDR, 10)
+        st = [L.spkadd_batch_create(ctypes.byref(h), 0, {most}, 1000, 1000, None)]
+        st.append(L.spkadd_batch_run(h, ctypes.byref(q), 1, 0, stream(0)))
+        out = [st, [x[0] for x in log() if x[0] == "refused"], F.fake_blocks(b"k_batch_scan")]
+        L.spkadd_batch_destroy(h)
+    """)
+    assert out[0] == [0, 0] and out[1] == [] and most <= out[2] <= most + 1
+
+
 # ---- events ----
 
 def test_events_stay_on_their_device(run):
